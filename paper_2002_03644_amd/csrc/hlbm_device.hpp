@@ -30,8 +30,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#if !defined(HLBM_REAL) || !defined(HLBM_NS)
-#error "define HLBM_REAL and HLBM_NS before including hlbm_device.hpp"
+#if !defined(HLBM_REAL) || !defined(HLBM_NS) || !defined(HLBM_IS_F32)
+#error "define HLBM_REAL, HLBM_NS and HLBM_IS_F32 before including hlbm_device.hpp"
 #endif
 
 namespace hlbm {
@@ -53,6 +53,14 @@ struct DomainArgs {
   real rho_ref, theta_ref, log_rho_ref, s_ref;
   real fref[kQ];       // deviation reference populations (zero in the FP64 form)
   real wall_u_lo, wall_u_hi, wall_theta;  // bcy == kBcWall: wall velocities, temperature
+  // constants of the step formed once on the host (see node_theta and collide)
+  real th_off;         // theta - lapv: theta_ref with the precise-theta flag, else 0
+  real eps_u;          // sgn_eps, infinite for the centred E1
+  real sigma1;         // 1 - sigma
+  real half_mu, mu9;   // mu / 2, mu / 9
+  real e2h, e2k;       // E2's factor: (2 - gamma) / 2, and times cs2 / 18; zero without E2
+  real cref;           // cs2 (theta_ref - 1)
+  real k4;             // 9 / 4, zero for the third-order expansion
 };
 
 // State offset (within a plane) of node i = y nx + x of the dense [ny][nx]
@@ -90,10 +98,23 @@ __device__ __forceinline__ int map_index(int v, int n, int bc) {
   return v < 0 ? 0 : (v >= n ? n - 1 : v);
 }
 
+__device__ __forceinline__ float fma_r(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_r(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float min_r(float a, float b) { return __builtin_fminf(a, b); }
+__device__ __forceinline__ double min_r(double a, double b) { return __builtin_fmin(a, b); }
 __device__ __forceinline__ float rcp_fast(float x) { return __builtin_amdgcn_rcpf(x); }
-__device__ __forceinline__ double rcp_fast(double x) { return 1.0 / x; }
+// The hardware seed has about half the bits; two Newton-Raphson steps on the
+// residual 1 - x r bring it within about half a unit in the last place, in 5
+// instructions against 12 of the IEEE division (which also handles zero,
+// infinities and subnormals, where this gives NaN: the operands here are
+// densities, pressures and limited sums of squares of a state that is flagged
+// when it is not positive and finite).
+__device__ __forceinline__ double rcp_fast(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+  return __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
+}
 __device__ __forceinline__ float div_fast(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
-__device__ __forceinline__ double div_fast(double a, double b) { return a / b; }
 __device__ __forceinline__ float exp_r(float x) { return __expf(x); }
 __device__ __forceinline__ double exp_r(double x) { return exp(x); }
 __device__ __forceinline__ float log_r(float x) { return __logf(x); }
@@ -150,11 +171,12 @@ struct NodeMoments {
 
 __device__ __forceinline__ NodeMoments node_moments(const real F[kQ], const DomainArgs &d) {
   NodeMoments m;
-  real r = ((F[0] + F[1]) + (F[2] + F[3])) + ((F[4] + F[5]) + (F[6] + F[7])) + F[8];
+  const real r = ((F[0] + F[1]) + (F[2] + F[3])) + ((F[4] + F[5]) + (F[6] + F[7])) + F[8];
   m.dr = r;
   m.rho = r + d.rho_ref;
-  m.jx = ((F[1] - F[3]) + (F[5] - F[7])) + (F[8] - F[6]);
-  m.jy = ((F[2] - F[4]) + (F[5] - F[7])) + (F[6] - F[8]);
+  const real d57 = F[5] - F[7];
+  m.jx = ((F[1] - F[3]) + d57) + (F[8] - F[6]);
+  m.jy = ((F[2] - F[4]) + d57) + (F[6] - F[8]);
   const real diag = (F[5] + F[6]) + (F[7] + F[8]);
   m.pxx = (F[1] + F[3]) + diag;
   m.pyy = (F[2] + F[4]) + diag;
@@ -162,9 +184,20 @@ __device__ __forceinline__ NodeMoments node_moments(const real F[kQ], const Doma
   return m;
 }
 
+// Natural logarithm of a normal number from the hardware's base-two one, the
+// product with ln 2 = hi + lo kept to the last bit.  Zero and infinity give NaN
+// (the densities it is taken of flag the state then either way).
+__device__ __forceinline__ float log_normal(float x) {
+  const float y = __builtin_amdgcn_logf(x);
+  constexpr float hi = 0x1.62e42ep-1f, lo = 0x1.efa39ep-25f;
+  const float r = y * hi;
+  return r + fma_r(y, lo, fma_r(y, hi, -r));
+}
+__device__ __forceinline__ double log_normal(double x) { return log(x); }
+
 // theta from the stored entropy (deviation form: ds = s - s_ref).
 __device__ __forceinline__ real node_theta(real rho, real sv, const DomainArgs &d) {
-  return d.theta_ref * exp_r(sv * d.inv_cv + d.gm1 * (log_r(rho) - d.log_rho_ref));
+  return d.theta_ref * exp_r(sv * d.inv_cv + d.gm1 * (log_normal(rho) - d.log_rho_ref));
 }
 
 // theta - theta_ref with relative accuracy on the deviation itself:
@@ -212,24 +245,244 @@ __device__ __forceinline__ double node_dtheta(double dr, double rho, double sv,
 __device__ __forceinline__ real tiny_sq() { return sizeof(real) == 4 ? real(1e-30) : real(1e-300); }
 __device__ __forceinline__ real van_albada(real a, real b) {
   const real ab = a * b;
-  const real den = a * a + b * b;
-  return (ab > real(0) && den > tiny_sq()) ? div_fast(ab * (a + b), den) : real(0);
+  const real den = fma_r(a, a, b * b);
+  return (ab > real(0) && den > tiny_sq()) ? (ab * (a + b)) * rcp_fast(den) : real(0);
 }
 
-// Upwind MUSCL derivative scaled by |u|: for u > 0 the stencil (q_{-1}, q0,
-// q1, q2) = (s_{i+1}, s_i, s_{i-1}, s_{i-2}); for u < 0 the mirror image.
-// Both signs reduce to |u| [(q0 - q1) + (slope(q0) - slope(q1)) / 2] by the
-// odd symmetry of the limiter.  u = 0 gives 0.
-__device__ __forceinline__ real muscl_term(real u, real sm2, real sm1, real s0, real sp1,
-                                           real sp2) {
+// Upwind MUSCL derivative u ds/dx at a node from the four differences around it,
+// dmm = s-1 - s-2, dm = s0 - s-1, dp = s1 - s0, dpp = s2 - s1: u > 0 takes u [dm
+// + (slope(dm, dp) - slope(dmm, dm)) / 2], u < 0 the mirror image, u = 0 gives 0.
+__device__ __forceinline__ real muscl(real u, real dmm, real dm, real dp, real dpp) {
   const bool pos = u > real(0);
-  const real qm1 = pos ? sp1 : sm1;
-  const real q1 = pos ? sm1 : sp1;
-  const real q2 = pos ? sm2 : sp2;
-  const real d01 = s0 - q1;
-  const real sl0 = van_albada(d01, qm1 - s0);
-  const real sl1 = van_albada(q1 - q2, d01);
-  return __builtin_fabs(u) * (d01 + real(0.5) * (sl0 - sl1));
+  const real d01 = pos ? dm : dp;
+  const real sl0 = van_albada(d01, pos ? dp : dm);
+  const real sl1 = van_albada(pos ? dmm : dpp, d01);
+  return u * fma_r(real(0.5), sl0 - sl1, d01);
+}
+
+// Fourier and viscous heat over rho theta.
+__device__ __forceinline__ real heat_term(const DomainArgs &d, real lap, real phi, real pt) {
+  return fma_r(d.lambda, lap, phi) * rcp_fast(pt);
+}
+
+// Laplacian of theta (or of theta - theta_ref, the same).
+__device__ __forceinline__ real laplacian(real c, real e, real w, real n, real s) {
+  return fma_r(real(-4), c, (e + w) + (n + s));
+}
+
+// What a node's neighbours and its own collision need of its moments.  lapv:
+// theta, or theta - theta_ref accurate relative to itself with the
+// precise-theta flag (the Laplacian's constant shift cancels); theta = lapv +
+// th_off either way.
+struct NodeState {
+  real dr, ux, uy, lapv, pxx, pyy, pxy;
+};
+
+// Running divergence check of a lane's nodes: least density and temperature,
+// and a sum that is NaN once a velocity or temperature was not finite.
+struct Health {
+  real least = real(1), acc = real(0);
+  __device__ __forceinline__ void add(real rho, real ux, real uy, real th) {
+    least = min_r(min_r(least, rho), th);
+    acc = fma_r((ux + uy) + th, real(0), acc);
+  }
+  __device__ __forceinline__ bool bad() const { return !(least > real(0)) || acc != acc; }
+};
+
+// Moments, theta and Gamma of one node from its nine populations and entropy.
+__device__ __forceinline__ NodeState node_state(const DomainArgs &d, const real (&F)[kQ],
+                                                const real sv, Health &health, real &gx,
+                                                real &gy) {
+  const NodeMoments m = node_moments(F, d);
+  const real inv_rho = rcp_fast(m.rho);
+  NodeState o;
+  o.dr = m.dr;
+  o.pxx = m.pxx;
+  o.pyy = m.pyy;
+  o.pxy = m.pxy;
+  o.ux = m.jx * inv_rho;
+  o.uy = m.jy * inv_rho;
+  real th;
+  if (d.flags & kFlagPreciseTheta) {
+    o.lapv = node_dtheta(m.dr, m.rho, sv, d);
+    th = o.lapv + d.th_off;
+  } else {
+    th = o.lapv = node_theta(m.rho, sv, d);
+  }
+  const real omt = real(1) - th;
+  gx = m.rho * o.ux * fma_r(-o.ux, o.ux, omt);
+  gy = m.rho * o.uy * fma_r(-o.uy, o.uy, omt);
+  health.add(m.rho, o.ux, o.uy, th);
+  return o;
+}
+
+// Neighbour values of a collision: velocities and Gamma of the four neighbours,
+// and Gamma of the node itself.
+struct NodeStencil {
+  real uxe, uxw, uxn, uxs, uye, uyw, uyn, uys, gxe, gxc, gxw, gyn, gyc, gys;
+};
+
+// E1 of one axis: the difference of Gamma upwind of the node's velocity,
+// centred inside the rounding band (or everywhere with the centred flag, whose
+// band is infinite), as one difference of selected values.
+__device__ __forceinline__ real upwind_gamma(const DomainArgs &d, real u, real gw, real gc,
+                                             real ge) {
+  const bool back = u > d.eps_u, fore = u < -d.eps_u;
+  const real diff = (back ? gc : ge) - (fore ? gc : gw);
+  return (back || fore ? real(1) : real(0.5)) * diff;
+}
+
+// Gradients, correction term, HRR stress and the nine post-collision
+// populations of one node, with its viscous heat phi and rho theta (pt).  sg,
+// sg1: sigma and 1 - sigma.  One result wherever it is inlined: FP32 leaves the
+// fused multiply-adds to the compiler (within an expression only), FP64 writes
+// them out.
+//
+// FP64: in absolute populations and few operations.
+//   - with tp = taubar p = mu + p / 2, 1 - 1/taubar = (mu - p / 2) / tp and
+//     tau / taubar = mu / tp: one reciprocal in place of three divisions;
+//   - the recursion and the Hermite coefficients are linear in a1, so a1 is
+//     multiplied by 1 - 1/taubar first; with X = ux^2 + c, Y = uy^2 + c,
+//     b = (1 - 1/taubar) a1:
+//       Axxy  = uy (rho ux^2 + rho c + bxx) + 2 ux bxy,
+//       Axxyy = Y (rho ux^2 + bxx) + X byy + rho c uy^2 + 4 ux uy bxy + rho c^2;
+//   - every coefficient carries the factor 1/9 of the projection from the
+//     start (rho / 9, (1 - 1/taubar) / 9, ...), which leaves the projection
+//     factors that are exact in binary.
+// FP32: deviations from the rest reference formed from deviations (p - p_ref,
+// rho c - rho_ref c_ref, rho c^2 - rho_ref c_ref^2).  Its rounding is kept term
+// by term: E1 is discontinuous in the sign of u, so where a velocity crosses
+// zero another rounding anywhere flips nodes (a 256^2 flow with steep
+// gradients: 1e-3 of the velocity at single nodes after 50 steps).
+__device__ __forceinline__ void collide(const DomainArgs &d, const NodeState &o,
+                                        const NodeStencil &n, const real sg, const real sg1,
+                                        real (&f)[kQ], real &phi, real &pt) {
+#if HLBM_IS_F32
+  const real cs2 = real(kCs2);
+  const real ux = o.ux, uy = o.uy, th = o.lapv + d.th_off, rho = o.dr + d.rho_ref;
+  // doubled velocity gradients (their factors 1/2 are exact wherever they go)
+  const real gxx = n.uxe - n.uxw, gxy = n.uye - n.uyw;
+  const real gyx = n.uxn - n.uxs, gyy = n.uyn - n.uys;
+  const real S = gxx - gyy, T = gyx + gxy;
+  const real p = rho * cs2 * th;
+  const real dth = th - d.theta_ref;
+  const real dp = cs2 * (o.dr * th + d.rho_ref * dth);  // p - p_ref
+  const real tau = d.mu * rcp_fast(p);
+  const real taub = tau + real(0.5);
+  const real itaub = rcp_fast(taub);
+  const real e2 = d.e2h * p * (gxx + gyy);
+  const real Exx = upwind_gamma(d, ux, n.gxw, n.gxc, n.gxe) + e2;
+  const real Eyy = upwind_gamma(d, uy, n.gys, n.gyc, n.gyn) + e2;
+  const real rux = rho * ux, ruy = rho * uy;
+  const real ruxx = rux * ux, ruyy = ruy * uy, ruxy = rux * uy;
+  // HRR stress
+  const real htp = real(-0.5) * (taub * p);
+  real a1xx = sg1 * (htp * S), a1yy = -a1xx, a1xy = sg1 * (htp * T);
+  if (sg != real(0)) {
+    const real prxx = (o.pxx - dp) - ruxx + real(0.5) * Exx;
+    const real pryy = (o.pyy - dp) - ruyy + real(0.5) * Eyy;
+    const real prxy = o.pxy - ruxy;
+    a1xx = sg * prxx + a1xx;
+    a1yy = sg * pryy + a1yy;
+    a1xy = sg * prxy + a1xy;
+  }
+  const real c = cs2 * (th - real(1));
+  const real ux2 = ux + ux, uy2 = uy + uy;
+  const real a1xxy = uy * a1xx + ux2 * a1xy;
+  const real a1xyy = ux * a1yy + uy2 * a1xy;
+  const real a1xxyy = real(2) * (ux * a1xyy + uy * a1xxy) + (c - ux * ux) * a1yy +
+                      (c - uy * uy) * a1xx - ux2 * uy2 * a1xy;
+  const real om = real(1) - itaub;
+  const real drc = dp - cs2 * o.dr;
+  const real dc = cs2 * dth;
+  const real drc2 = o.dr * c * c + d.rho_ref * dc * (c + d.cref);
+  const real Axx = ruxx + drc + om * a1xx + real(0.5) * Exx;
+  const real Ayy = ruyy + drc + om * a1yy + real(0.5) * Eyy;
+  const real Axy = ruxy + om * a1xy;
+  const real rc = rho * c;
+  const real Axxy = ruxx * uy + rc * uy + om * a1xxy;
+  const real Axyy = ruyy * ux + rc * ux + om * a1xyy;
+  const real Axxyy = (d.flags & kFlagFeq3)
+                         ? real(0)
+                         : ruxx * uy * uy + rc * (ux * ux + uy * uy) + drc2 + om * a1xxyy;
+  project(o.dr, rux, ruy, Axx, Axy, Ayy, Axxy, Axyy, Axxyy, f);
+  if (d.flags & kFlagPhiFD) {
+    const real aa = real(0.5) * S, bb = real(0.5) * T;
+    phi = d.mu * (aa * aa + bb * bb);
+  } else {
+    phi = (real(-0.5) * (tau * itaub)) * (a1xx * gxx + a1xy * T + a1yy * gyy);
+  }
+  pt = rho * th;
+#else
+  constexpr real cs2 = real(kCs2), c9 = real(1.0 / 9.0);
+  const real ux = o.ux, uy = o.uy;
+  const real th = o.lapv + d.th_off;
+  const real rho = o.dr;
+  // doubled velocity gradients
+  const real gxx = n.uxe - n.uxw, gxy = n.uye - n.uyw;
+  const real gyx = n.uxn - n.uxs, gyy = n.uyn - n.uys;
+  const real S = gxx - gyy, T = gyx + gxy;
+  pt = rho * th;
+  const real tp = fma_r(pt, real(0.5 * kCs2), d.mu);
+  const real rtp = rcp_fast(tp);
+  const real om9 = fma_r(pt, real(-0.5 * kCs2 / 9.0), d.mu9) * rtp;
+  const real c = fma_r(th, cs2, -cs2);
+  const real rho9 = rho * c9;
+  const real rc9 = rho9 * c;
+  const real dp9 = real(kCs2 / 9.0) * pt;
+  // (E1 + E2) / 18
+  const real e1x = upwind_gamma(d, ux, n.gxw, n.gxc, n.gxe);
+  const real e1y = upwind_gamma(d, uy, n.gys, n.gyc, n.gyn);
+  const real e2 = d.e2k * (pt * (gxx + gyy));
+  const real hEx = fma_r(e1x, real(0.5 / 9.0), e2);
+  const real hEy = fma_r(e1y, real(0.5 / 9.0), e2);
+  const real rux = rho9 * ux, ruy = rho9 * uy;
+  const real uxx = ux * ux, uyy = uy * uy;
+  const real ruxx = rho9 * uxx, ruyy = rho9 * uyy, ruxy = rux * uy;
+  // HRR stress
+  const real fd = sg1 * fma_r(pt, real(-0.25 * kCs2), -d.half_mu);
+  const real fS = fd * S, fT = fd * T;
+  const real prxx = fma_r(real(-9), (dp9 + ruxx) - hEx, o.pxx);
+  const real pryy = fma_r(real(-9), (dp9 + ruyy) - hEy, o.pyy);
+  const real prxy = fma_r(real(-9), ruxy, o.pxy);
+  const real axx = fma_r(sg, prxx, fS), ayy = fma_r(sg, pryy, -fS), axy = fma_r(sg, prxy, fT);
+  if (d.flags & kFlagPhiFD) {
+    phi = (real(0.5) * d.half_mu) * fma_r(S, S, T * T);
+  } else {
+    phi = -(d.half_mu * rtp) * fma_r(axx, gxx, fma_r(axy, T, ayy * gyy));
+  }
+  const real bxx = om9 * axx, byy = om9 * ayy, bxy = om9 * axy;
+  const real Nx = ruxx + bxx, Ny = ruyy + byy;
+  const real Axx = Nx + (rc9 + hEx), Ayy = Ny + (rc9 + hEy), Axy = ruxy + bxy;
+  const real ux2 = ux + ux, uy2 = uy + uy;
+  const real P1 = ux2 * bxy, P2 = uy2 * bxy;
+  const real Axxy = fma_r(uy, Nx + rc9, P1), Axyy = fma_r(ux, Ny + rc9, P2);
+  const real X = uxx + c, Y = uyy + c;
+  const real Axxyy =
+      fma_r(Y, Nx, fma_r(rc9, uyy, fma_r(X, byy, fma_r(uy2, P1, rc9 * c))));
+  // projection on the nine populations
+  const real s = Axx + Ayy;
+  const real Z = d.k4 * Axxyy;
+  const real W = fma_r(real(-1.5), s, rho9);
+  f[0] = real(4) * (W + Z);
+  const real v = fma_r(real(-2), Z, W);
+  const real px = fma_r(real(4.5), Axx, v), py = fma_r(real(4.5), Ayy, v);
+  const real ox = fma_r(real(-4.5), Axyy, real(3) * rux);
+  const real oy = fma_r(real(-4.5), Axxy, real(3) * ruy);
+  f[1] = px + ox;
+  f[3] = px - ox;
+  f[2] = py + oy;
+  f[4] = py - oy;
+  const real bd = fma_r(real(0.75), s, fma_r(real(0.25), rho9, Z));
+  const real dxy = real(2.25) * Axy;
+  const real dx = fma_r(real(2.25), Axyy, real(0.75) * rux);
+  const real dy = fma_r(real(2.25), Axxy, real(0.75) * ruy);
+  const real ep = bd + dxy, em = bd - dxy, gp = dx + dy, gm = dx - dy;
+  f[5] = ep + gp;
+  f[7] = ep - gp;
+  f[6] = em - gm;
+  f[8] = em + gm;
+#endif
 }
 
 // --------------------------------------------------------------- the step
@@ -240,42 +493,172 @@ __device__ __forceinline__ real muscl_term(real u, real sm2, real sm1, real s0, 
 // holds the four halo columns (x0-2, x0-1, x0+CW, x0+CW+1) on its first four
 // lanes.  In the LDS rings a column sits at position ri = column - (x0 - 2).
 // Each lane sweeps the rows of the strip through three stages:
-//   A(j)    moments of row j from the ten planes: u, theta, Gamma and s go
-//           into LDS rings, rho and Pi stay in registers;
-//   B(k)    gradients, E, a1 and the nine post-collision populations of row
-//           k (radius-1 stencil through the rings): the six with c_x != 0
-//           into LDS rings, the three with c_x = 0 into the lane's registers;
-//   C(k)    pull streaming of row k out of those and its entropy update
-//           (radius-2 stencil), storing both.
-// Iteration i issues the loads of row i+1, runs B(i-1), a barrier, A(i+1) on
-// those loads, C(i-2), and a second barrier.  Loads are thus consumed in the
-// iteration that issued them, after the B work that hides their latency, and
-// before C's stores (a wait placed after stores that sit under a branch
-// would also wait for the stores).  Each node's moments and collision are
-// computed once per step (plus a 4-column halo); HBM sees one read and one
-// write of the state.
+//   A(j)  moments of row j from the ten planes: u, Gamma_x, theta and s go into
+//         LDS rings, the rest stays in registers;
+//   B(k)  collision of row k (radius-1 stencil: x-neighbours through the rings,
+//         y-neighbours from the lane's registers), its heat and the x part of
+//         its entropy's advection: the six populations with c_x != 0 into LDS
+//         rings, the rest into the lane's registers;
+//   C(k)  pull streaming of row k out of those and its entropy update, storing
+//         both.
+// Iteration i runs A(i+1) and B(i), a barrier, issues the loads of row i+2 and
+// runs C(i-1), and a second barrier: B(i) needs its x-neighbours of row i (of
+// the previous iteration) and its own column's rows i-1 .. i+1, so it follows
+// A(i+1) without a barrier and only one row of node state is carried.
 //
-// Ring depths are the smallest the two barriers per iteration allow (only a
-// write of A(i+1) may overlap a read of C(i-2) of another wave):
-//   u_x, u_y, Gamma_x: 2 rows (B reads the x-neighbours of row k; rows k-1
-//   and k+1 of its own column, and Gamma_y entirely, come from registers);
-//   theta: 5 (C reads rows k-1 and k+1);  s: 6 (C reads rows k-2..k+2);
-//   post-collision populations by the row they stream from: c_y = 0 -> 2,
-//   c_y = +1 (read one row later) -> 3, c_y = -1 (read in the same row) -> 1;
-//   in registers the same delays: population 0 one row, 2 two rows, 4 none.
-// 29 rows of CW + 4 floats in all: 22.7 KB at CW = 192, seven workgroups per
-// CU.
-// Shared memory of one tile sweep.
-template <int CW>
-struct TileRings {
-  static constexpr int W = CW + 4;  // ring width: tile plus halo
-  real ux[2][W], uy[2][W], gx[2][W];
-  real th[5][W], s[6][W];
-  // post-collision populations that stream across columns; 0, 2 and 4
-  // (c_x = 0) stay in their lane's registers
+// The x part of the entropy's advection reads only row k's own s, so B forms
+// it; C has the y part from the lane's last four differences of s, which pass
+// from row to row in registers.
+//
+// Ring depths are the smallest the two barriers allow: u_x, u_y, Gamma_x, theta
+// and s two rows (A(i+1) writes while B(i) reads), populations by the row they
+// stream from: c_y = 0 -> 2, c_y = +1 (read one row later) -> 3, c_y = -1 -> 1.
+// 22 rows in all: 17.8 KB at CW = 192 in FP32.
+//
+// Every lane runs every stage of every row, also where a stencil reaches past
+// the ring or a row's inputs are not there yet: such values are read by no
+// valid node, and without branches around the stages their results need no
+// merging (a third of the sweep's instructions were moves).  `lo` and `hi` keep
+// those reads of a ring's neighbours inside the structure.  Only loads and
+// stores look at the lane, and the divergence check counts valid nodes only.
+template <int W>
+struct LevelRings {
+  real lo[64];
+  real ux[2][W], uy[2][W], gx[2][W], th[2][W], s[2][W];
   real f0[2][2][W];  // populations 1, 3   (c_y =  0)
   real fp[3][2][W];  // populations 5, 6   (c_y = +1)
   real fm[2][W];     // populations 7, 8   (c_y = -1)
+  real hi[64];
+};
+
+// Per-lane registers of one time level.
+struct LevelRegs {
+  // A -> B: the newest row (n), B's row (c) and the row below it (m); ds: s minus
+  // the row below's
+  real n_dr = 0, n_pxx = 0, n_pyy = 0, n_pxy = 0, n_ux = 0, n_uy = 0, n_th = 1, n_gx = 0, n_gy = 0;
+  real n_s = 0, n_ds = 0;
+  real c_dr = 0, c_pxx = 0, c_pyy = 0, c_pxy = 0, c_ux = 0, c_uy = 0, c_th = 1, c_gx = 0, c_gy = 0;
+  real c_s = 0, c_ds = 0;
+  real m_ux = 0, m_uy = 0, m_th = 1, m_gy = 0;
+  real p_s = 0, p_ds = 0, q_ds = 0;  // s and ds of the rows below
+  // B -> C: last B row (b), the row below it (p), and of two rows below (q)
+  real b_adv = 0, b_heat = 0, b_vy = 0, b_f0 = 0, b_f2 = 0, b_f4 = 0;
+  real p_adv = 0, p_heat = 0, p_vy = 0, p_f0 = 0, p_f2 = 0, q_f2 = 0;
+};
+
+// A(j): moments of one node of row j from its nine populations and entropy.
+template <int W>
+__device__ __forceinline__ void level_a(const DomainArgs &d, LevelRegs &g, LevelRings<W> &R,
+                                        const int j, const int ri, const real (&F)[kQ],
+                                        const real sv, Health &health) {
+  const int z = j & 1;
+  real gx, gy;
+  const NodeState o = node_state(d, F, sv, health, gx, gy);
+  R.ux[z][ri] = o.ux;
+  R.uy[z][ri] = o.uy;
+  R.gx[z][ri] = gx;
+  R.th[z][ri] = o.lapv;
+  R.s[z][ri] = sv;
+  g.m_ux = g.c_ux;
+  g.m_uy = g.c_uy;
+  g.m_th = g.c_th;
+  g.m_gy = g.c_gy;
+  g.c_dr = g.n_dr;
+  g.c_pxx = g.n_pxx;
+  g.c_pyy = g.n_pyy;
+  g.c_pxy = g.n_pxy;
+  g.c_ux = g.n_ux;
+  g.c_uy = g.n_uy;
+  g.c_th = g.n_th;
+  g.c_gx = g.n_gx;
+  g.c_gy = g.n_gy;
+  g.q_ds = g.p_ds;
+  g.p_ds = g.c_ds;
+  g.c_ds = g.n_ds;
+  g.n_ds = sv - g.n_s;
+  g.p_s = g.c_s;
+  g.c_s = g.n_s;
+  g.n_s = sv;
+  g.n_dr = o.dr;
+  g.n_pxx = o.pxx;
+  g.n_pyy = o.pyy;
+  g.n_pxy = o.pxy;
+  g.n_ux = o.ux;
+  g.n_uy = o.uy;
+  g.n_th = o.lapv;
+  g.n_gx = gx;
+  g.n_gy = gy;
+}
+
+// B(k): collision, heat and x advection of row k (row k + 1 was the last A).
+template <int W>
+__device__ __forceinline__ void level_b(const DomainArgs &d, LevelRegs &g, LevelRings<W> &R,
+                                        const int k, const int ri, const real sg,
+                                        const real sg1) {
+  const int z = k & 1, sc = k % 3;
+  NodeStencil n;
+  n.uxe = R.ux[z][ri + 1];
+  n.uxw = R.ux[z][ri - 1];
+  n.uye = R.uy[z][ri + 1];
+  n.uyw = R.uy[z][ri - 1];
+  n.gxe = R.gx[z][ri + 1];
+  n.gxw = R.gx[z][ri - 1];
+  n.uxn = g.n_ux;
+  n.uxs = g.m_ux;
+  n.uyn = g.n_uy;
+  n.uys = g.m_uy;
+  n.gyn = g.n_gy;
+  n.gxc = g.c_gx;
+  n.gyc = g.c_gy;
+  n.gys = g.m_gy;
+  const real the = R.th[z][ri + 1], thw = R.th[z][ri - 1];
+  const real se = R.s[z][ri + 1], sw = R.s[z][ri - 1];
+  const real see = R.s[z][ri + 2], sww = R.s[z][ri - 2];
+  const NodeState o{g.c_dr, g.c_ux, g.c_uy, g.c_th, g.c_pxx, g.c_pyy, g.c_pxy};
+  real f[kQ], phi, pt;
+  collide(d, o, n, sg, sg1, f, phi, pt);
+  R.f0[z][0][ri] = f[1];
+  R.f0[z][1][ri] = f[3];
+  R.fp[sc][0][ri] = f[5];
+  R.fp[sc][1][ri] = f[6];
+  R.fm[0][ri] = f[7];
+  R.fm[1][ri] = f[8];
+  g.q_f2 = g.p_f2;
+  g.p_adv = g.b_adv;
+  g.p_heat = g.b_heat;
+  g.p_vy = g.b_vy;
+  g.p_f0 = g.b_f0;
+  g.p_f2 = g.b_f2;
+  g.b_f0 = f[0];
+  g.b_f2 = f[2];
+  g.b_f4 = f[4];
+  g.b_vy = o.uy;
+  g.b_heat = heat_term(d, laplacian(g.c_th, the, thw, g.n_th, g.m_th), phi, pt);
+  g.b_adv = muscl(o.ux, sw - sww, g.c_s - sw, se - g.c_s, see - se);
+}
+
+// C(k): pull streaming of row k and its entropy update (row k + 1 was the
+// last B).
+template <int W>
+__device__ __forceinline__ void level_c(const LevelRegs &g, const LevelRings<W> &R, const int k,
+                                        const int ri, real (&Fo)[kQ], real &snew) {
+  const int z = k & 1, pm = (k + 2) % 3;  // slot of row k in f0, of row k - 1 in fp
+  Fo[0] = g.p_f0;                  // row k, this column
+  Fo[1] = R.f0[z][0][ri - 1];
+  Fo[3] = R.f0[z][1][ri + 1];
+  Fo[2] = g.q_f2;                  // row k - 1, this column
+  Fo[5] = R.fp[pm][0][ri - 1];
+  Fo[6] = R.fp[pm][1][ri + 1];
+  Fo[4] = g.b_f4;                  // row k + 1, this column
+  Fo[7] = R.fm[0][ri + 1];
+  Fo[8] = R.fm[1][ri - 1];
+  // row k's s and the differences around it; the newest A was row k + 2
+  snew = g.p_s - (g.p_adv + muscl(g.p_vy, g.q_ds, g.p_ds, g.c_ds, g.n_ds)) + g.p_heat;
+}
+
+template <bool kValue>
+struct Flag {
+  static constexpr bool value = kValue;
 };
 
 // Batched items: the skip of a frozen domain is decided once per item for
@@ -303,7 +686,8 @@ __device__ __forceinline__ bool barrier_skip(unsigned frozen) {
 template <int CW, bool kBatch = false>
 __device__ __forceinline__ void sweep_tile(const DomainArgs &d, const real *src0, real *dst0,
                                            unsigned *status, const int rows, const int bx,
-                                           const int by, const unsigned frozen, TileRings<CW> &R) {
+                                           const int by, const unsigned frozen,
+                                           LevelRings<CW + 4> &R) {
   const int t = threadIdx.x;
   const real *src[kPlanes];
   real *dst[kPlanes];
@@ -312,269 +696,73 @@ __device__ __forceinline__ void sweep_tile(const DomainArgs &d, const real *src0
     src[q] = src0 + (long long)q * d.plane;
     dst[q] = dst0 + (long long)q * d.plane;
   }
-  auto &r_ux = R.ux;
-  auto &r_uy = R.uy;
-  auto &r_gx = R.gx;
-  auto &r_th = R.th;
-  auto &r_s = R.s;
-  auto &r_f0 = R.f0;
-  auto &r_fp = R.fp;
-  auto &r_fm = R.fm;
   const int x0 = bx * CW, y0 = by * rows;
   // lane -> ring position: tile lanes at 2..CW+1, halo lanes at 0, 1, CW+2, CW+3
   const int h = t - CW;
   const int ri = t < CW ? t + 2 : (h < 2 ? h : (h < 4 ? CW + h : 0));
-  const bool a_lane = t < CW + 4;                        // loads and moments
-  const bool b_col = t < CW || h == 1 || h == 2;         // collision: ring 1..CW+2
   const int vx = x0 - 2 + ri;
   const int cx = map_index(vx, d.nx, d.bcx);
   const int nrow = min(rows, d.ny - y0);
-  const int nit = nrow + 4;
   const bool own_col = t < CW && vx < d.nx;
-  const real cs2 = real(kCs2);
-  const real cref = cs2 * (d.theta_ref - real(1));
   constexpr unsigned kEl = sizeof(real);
-  unsigned bad = 0;
+  Health health;
+  LevelRegs g;
 
   // 32-bit byte offset of virtual row j (x fastest) from the plane bases.
   auto row_off = [&](int j) {
     return (unsigned)(map_index(y0 - 2 + j, d.ny, d.bcy) * d.pitch + cx) * kEl;
   };
-
-  // Node state of rows k (s0_*) and k+1 (s1_*) carried from A to B.
-  real s0_dr = 0, s0_rho = 1, s0_pxx = 0, s0_pyy = 0, s0_pxy = 0, s0_ux = 0, s0_uy = 0, s0_th = 1;
-  real s1_dr = 0, s1_rho = 1, s1_pxx = 0, s1_pyy = 0, s1_pxy = 0, s1_ux = 0, s1_uy = 0, s1_th = 1;
-  // B's stencil along y within the lane's own column, in registers: u of row
-  // k-1 and Gamma_y = rho u_y (1 - theta - u_y^2) of rows k-1, k, k+1
-  real m_ux = 0, m_uy = 0, m_gy = 0, c_gy = 0, n_gy = 0;
-  // B -> C carry: B(k) fills nB_*, copied to cB_* at the end of the
-  // iteration, read by C(k) in the next one.
-  real nB_ux = 0, nB_uy = 0, nB_rho = 1, nB_th = 1, nB_phi = 0;
-  real cB_ux = 0, cB_uy = 0, cB_rho = 1, cB_th = 1, cB_phi = 0;
-  // populations 0, 2, 4 of B's rows kept in registers: nB_* of row k (this
-  // iteration's B), cB_f0 of row k-1, cB_f2 of row k-1, cB_f2b of row k-2
-  real nB_f0 = 0, nB_f2 = 0, nB_f4 = 0, cB_f0 = 0, cB_f2 = 0, cB_f2b = 0;
-
-  // A(j): moments of one row from its ten loaded planes.
-  auto stage_a = [&](const int j, const real (&ld)[kPlanes]) {
+  real ld[kPlanes];
+  auto load_row = [&](int j) {
+    const unsigned off = row_off(j);
+#pragma unroll
+    for (int q = 0; q < kPlanes; ++q) ld[q] = load_at(src[q], off);
+  };
+  auto stage_a = [&](int j) {
     real F[kQ];
 #pragma unroll
     for (int q = 0; q < kQ; ++q) F[q] = ld[q];
-    const real sv = ld[9];
-    const NodeMoments m = node_moments(F, d);
-    const real inv_rho = rcp_fast(m.rho);
-    const real ux = m.jx * inv_rho, uy = m.jy * inv_rho;
-    // The Fourier term's Laplacian is taken of what the theta ring holds:
-    // theta itself by default, theta - theta_ref (accurate relative to
-    // itself) with the precise-theta flag; the constant shift cancels.
-    real th, lap_val;
-    if (d.flags & kFlagPreciseTheta) {
-      lap_val = node_dtheta(m.dr, m.rho, sv, d);
-      th = d.theta_ref + lap_val;
-    } else {
-      th = node_theta(m.rho, sv, d);
-      lap_val = th;
-    }
-    r_ux[j & 1][ri] = ux;
-    r_uy[j & 1][ri] = uy;
-    r_th[j % 5][ri] = lap_val;
-    r_gx[j & 1][ri] = m.rho * ux * ((real(1) - th) - ux * ux);
-    r_s[j % 6][ri] = sv;
-    m_ux = s0_ux;
-    m_uy = s0_uy;
-    m_gy = c_gy;
-    c_gy = n_gy;
-    n_gy = m.rho * uy * ((real(1) - th) - uy * uy);
-    s0_dr = s1_dr;
-    s0_rho = s1_rho;
-    s0_pxx = s1_pxx;
-    s0_pyy = s1_pyy;
-    s0_pxy = s1_pxy;
-    s0_ux = s1_ux;
-    s0_uy = s1_uy;
-    s0_th = s1_th;
-    s1_dr = m.dr;
-    s1_rho = m.rho;
-    s1_pxx = m.pxx;
-    s1_pyy = m.pyy;
-    s1_pxy = m.pxy;
-    s1_ux = ux;
-    s1_uy = uy;
-    s1_th = th;
-    bad |= (m.rho > real(0) && th > real(0) && __builtin_isfinite(ux + uy + th)) ? 0u : 1u;
+    level_a(d, g, R, j, ri, F, ld[9], health);
   };
 
-  if (a_lane) {  // prologue: A(0)
-    real ld[kPlanes];
-    const unsigned off = row_off(0);
+  // A(i + 1), B(i), a barrier, the loads of row i + 2 and (kOut) C(i - 1).  The
+  // loads come before C's stores: a wait for them never waits for this row's
+  // stores as well.
+  auto row = [&](const int i, auto kOut) {
+    stage_a(i + 1);
+    // wall rows take the projected stress alone: their rebuilt populations
+    // carry the wall's finite-difference stress
+    const int yk = y0 - 2 + i;
+    const bool wall_row = d.bcy == kBcWall && (yk == 0 || yk == d.ny - 1);
+    level_b(d, g, R, i, ri, wall_row ? real(1) : d.sigma, wall_row ? real(0) : d.sigma1);
+    __syncthreads();
+    if (i + 2 <= nrow + 3) load_row(i + 2);
+    if constexpr (kOut.value) {
+      real Fo[kQ], snew;
+      level_c(g, R, i - 1, ri, Fo, snew);
+      if (own_col) {
+        const unsigned off = (unsigned)((y0 + i - 3) * d.pitch + vx) * kEl;
 #pragma unroll
-    for (int q = 0; q < kPlanes; ++q) ld[q] = load_at(src[q], off);
-    stage_a(0, ld);
-  }
-  if (barrier_skip<kBatch>(frozen)) return;
-
-  for (int i = 0; i < nit; ++i) {
-    // ---------------- issue the loads of row i+1 (consumed by A after B)
-    real ld[kPlanes];
-    const bool do_a = a_lane && i + 1 < nit;
-    if (do_a) {
-      const unsigned off = row_off(i + 1);
-#pragma unroll
-      for (int q = 0; q < kPlanes; ++q) ld[q] = load_at(src[q], off);
-    }
-    // A(i) has run for rows 0..i; s1_* holds row i, s0_* row i-1.
-
-    // ---------------- B(k), k = i-1: collision
-    if (i >= 2) {
-      const int k = i - 1;
-      const int sc = k % 3;
-      if (b_col) {
-        const real rho = s0_rho, ux = s0_ux, uy = s0_uy, th = s0_th;
-        const int su = k & 1;
-        const real uxe = r_ux[su][ri + 1], uxw = r_ux[su][ri - 1];
-        const real uye = r_uy[su][ri + 1], uyw = r_uy[su][ri - 1];
-        const real uxn = s1_ux, uxs = m_ux;
-        const real uyn = s1_uy, uys = m_uy;
-        const real dxux = real(0.5) * (uxe - uxw), dxuy = real(0.5) * (uye - uyw);
-        const real dyux = real(0.5) * (uxn - uxs), dyuy = real(0.5) * (uyn - uys);
-        const real div = dxux + dyuy;
-        const real p = rho * cs2 * th;
-        const real dth = th - d.theta_ref;
-        const real dp = cs2 * (s0_dr * th + d.rho_ref * dth);  // p - p_ref
-        const real tau = div_fast(d.mu, p);
-        const real taub = tau + real(0.5);
-        const real itaub = rcp_fast(taub);
-        // E1 (upwind in the sign of the node velocity; centred inside the band)
-        const real gc = r_gx[k & 1][ri];
-        const real gxe = r_gx[k & 1][ri + 1], gxw = r_gx[k & 1][ri - 1];
-        const real gcy = c_gy;
-        const real gyn = n_gy, gys = m_gy;
-        real e1x, e1y;
-        if (d.flags & kFlagE1Centred) {
-          e1x = real(0.5) * (gxe - gxw);
-          e1y = real(0.5) * (gyn - gys);
-        } else {
-          const real ep = d.sgn_eps;
-          e1x = ux > ep ? gc - gxw : (ux < -ep ? gxe - gc : real(0.5) * (gxe - gxw));
-          e1y = uy > ep ? gcy - gys : (uy < -ep ? gyn - gcy : real(0.5) * (gyn - gys));
-        }
-        const real e2 = (d.flags & kFlagE2Off) ? real(0) : d.e2c * p * div;
-        const real Exx = e1x + e2, Eyy = e1y + e2;
-        // HRR stress
-        const real rux = rho * ux, ruy = rho * uy;
-        const real ruxx = rux * ux, ruyy = ruy * uy, ruxy = rux * uy;
-        const real prxx = (s0_pxx - dp) - ruxx + real(0.5) * Exx;
-        const real pryy = (s0_pyy - dp) - ruyy + real(0.5) * Eyy;
-        const real prxy = s0_pxy - ruxy;
-        const real tp = taub * p;
-        const real fdxx = -tp * (dxux - dyuy);
-        const real fdxy = -tp * (dyux + dxuy);
-        // wall rows take the projected stress alone: their rebuilt populations
-        // carry the wall's finite-difference stress
-        const int yk = y0 - 2 + k;
-        const bool wall_row = d.bcy == kBcWall && (yk == 0 || yk == d.ny - 1);
-        const real sg = wall_row ? real(1) : d.sigma, sg1 = real(1) - sg;
-        const real a1xx = sg * prxx + sg1 * fdxx;
-        const real a1yy = sg * pryy - sg1 * fdxx;
-        const real a1xy = sg * prxy + sg1 * fdxy;
-        const real c = cs2 * (th - real(1));
-        const real a1xxy = uy * a1xx + real(2) * ux * a1xy;
-        const real a1xyy = ux * a1yy + real(2) * uy * a1xy;
-        const real a1xxyy = real(2) * (ux * a1xyy + uy * a1xxy) + (c - ux * ux) * a1yy +
-                            (c - uy * uy) * a1xx - real(4) * ux * uy * a1xy;
-        const real om = real(1) - itaub;
-        // rho c - rho_ref c_ref and rho c^2 - rho_ref c_ref^2 as deviations
-        const real drc = dp - cs2 * s0_dr;
-        const real dc = cs2 * dth;
-        const real drc2 = s0_dr * c * c + d.rho_ref * dc * (c + cref);
-        const real Axx = ruxx + drc + om * a1xx + real(0.5) * Exx;
-        const real Ayy = ruyy + drc + om * a1yy + real(0.5) * Eyy;
-        const real Axy = ruxy + om * a1xy;
-        const real rc = rho * c;
-        const real Axxy = ruxx * uy + rc * uy + om * a1xxy;
-        const real Axyy = ruyy * ux + rc * ux + om * a1xyy;
-        const real Axxyy = (d.flags & kFlagFeq3)
-                               ? real(0)
-                               : ruxx * uy * uy + rc * (ux * ux + uy * uy) + drc2 + om * a1xxyy;
-        real f[kQ];
-        project(s0_dr, rux, ruy, Axx, Axy, Ayy, Axxy, Axyy, Axxyy, f);
-        r_f0[k & 1][0][ri] = f[1];
-        r_f0[k & 1][1][ri] = f[3];
-        r_fp[sc][0][ri] = f[5];
-        r_fp[sc][1][ri] = f[6];
-        r_fm[0][ri] = f[7];
-        r_fm[1][ri] = f[8];
-        nB_f0 = f[0];
-        nB_f2 = f[2];
-        nB_f4 = f[4];
-        real phi;
-        if (d.flags & kFlagPhiFD) {
-          const real aa = dxux - dyuy, bb = dyux + dxuy;
-          phi = d.mu * (aa * aa + bb * bb);
-        } else {
-          phi = -(tau * itaub) * (a1xx * dxux + a1xy * (dyux + dxuy) + a1yy * dyuy);
-        }
-        nB_ux = ux;
-        nB_uy = uy;
-        nB_rho = rho;
-        nB_th = th;
-        nB_phi = phi;
+        for (int q = 0; q < kQ; ++q) store_stream(dst[q], off, Fo[q]);
+        store_stream(dst[9], off, snew);
       }
     }
     __syncthreads();
+  };
 
-    // ---------------- A(i+1) on the loads issued at the top.  It runs before
-    // C so that waiting for those loads never waits for C's stores as well
-    // (A writes ring slots of row i+1, which C does not read).
-    if (do_a) stage_a(i + 1, ld);
-
-    // ---------------- C(k), k = i-2: stream and entropy
-    if (i >= 4 && own_col) {
-      const int k = i - 2;
-      const int z = k & 1, pm = (k + 2) % 3;  // slot of row k in r_f0, of row k-1 in r_fp
-      real Fo[kQ];
-      Fo[0] = cB_f0;    // row k, this column
-      Fo[1] = r_f0[z][0][ri - 1];
-      Fo[3] = r_f0[z][1][ri + 1];
-      Fo[2] = cB_f2b;   // row k-1, this column
-      Fo[5] = r_fp[pm][0][ri - 1];
-      Fo[6] = r_fp[pm][1][ri + 1];
-      Fo[4] = nB_f4;    // row k+1, this column
-      Fo[7] = r_fm[0][ri + 1];
-      Fo[8] = r_fm[1][ri - 1];
-      const int s0 = k % 6, s1 = (k + 1) % 6, s2 = (k + 2) % 6, sm1 = (k + 5) % 6,
-                sm2 = (k + 4) % 6;
-      const real sc = r_s[s0][ri];
-      const real advx = muscl_term(cB_ux, r_s[s0][ri - 2], r_s[s0][ri - 1], sc, r_s[s0][ri + 1],
-                                   r_s[s0][ri + 2]);
-      const real advy = muscl_term(cB_uy, r_s[sm2][ri], r_s[sm1][ri], sc, r_s[s1][ri], r_s[s2][ri]);
-      const int t0 = k % 5, tn = (k + 1) % 5, ts = (k + 4) % 5;
-      // Laplacian of theta (or of theta - theta_ref, the same)
-      const real lap = ((r_th[t0][ri + 1] + r_th[t0][ri - 1]) + (r_th[tn][ri] + r_th[ts][ri])) -
-                       real(4) * r_th[t0][ri];
-      const real snew = sc - (advx + advy) + div_fast(d.lambda * lap + cB_phi, cB_rho * cB_th);
-      const unsigned off = (unsigned)((y0 + k - 2) * d.pitch + vx) * kEl;
-#pragma unroll
-      for (int q = 0; q < kQ; ++q) store_stream(dst[q], off, Fo[q]);
-      store_stream(dst[9], off, snew);
-    }
-    cB_ux = nB_ux;
-    cB_uy = nB_uy;
-    cB_rho = nB_rho;
-    cB_th = nB_th;
-    cB_phi = nB_phi;
-    cB_f2b = cB_f2;
-    cB_f2 = nB_f2;
-    cB_f0 = nB_f0;
-    __syncthreads();
-  }
-  if (bad) atomicOr(status, 1u);
+  load_row(0);
+  stage_a(0);
+  load_row(1);
+  if (barrier_skip<kBatch>(frozen)) return;
+  for (int i = 0; i < 3; ++i) row(i, Flag<false>());
+  for (int i = 3; i <= nrow + 2; ++i) row(i, Flag<true>());
+  if (health.bad()) atomicOr(status, 1u);
 }
 
 // Whole-domain step: one workgroup per tile.
 template <int CW>
 __global__ __launch_bounds__(CW + 64) void k_step(StepArgs a) {
-  __shared__ TileRings<CW> R;
+  __shared__ LevelRings<CW + 4> R;
   int bid = blockIdx.x;
   const int nblk = a.nbx * a.nby;
   if (a.xcd_remap) {
@@ -637,7 +825,7 @@ __device__ __forceinline__ TileWalk tile_walk(const int n, const int xcd) {
 
 template <int CW>
 __global__ __launch_bounds__(CW + 64) void k_step_batch(BatchArgs a) {
-  __shared__ TileRings<CW> R;
+  __shared__ LevelRings<CW + 4> R;
   const TileWalk walk = tile_walk(a.nitems, a.xcd_walk);
   for (int it = walk.first; it < walk.end; it += walk.step) {
     const int4 w = a.items[it];

@@ -121,10 +121,9 @@ __device__ __forceinline__ TileSlots<TW, TH, NT> tile_slots(const int t) {
   return S;
 }
 
-// Moments of one node kept by its owner from A to B and C.
-struct TileNode {
-  real dr, rho, pxx, pyy, pxy, ux, uy, th, sv;
-};
+// Moments of one node kept by its owner from A to B (what C needs again it
+// reads from LDS: registers, not LDS, limit the workgroups per compute unit).
+using TileNode = NodeState;
 
 // Issue the ten loads of every live slot of the tile at (x0, y0).
 template <int TW, int TH, int NT>
@@ -170,7 +169,7 @@ template <int TW, int TH, int NT>
 __device__ __forceinline__ void tile_a(const DomainArgs &d, const TileSlots<TW, TH, NT> &S,
                                        const real (&ld)[TileGeom<TW, TH, NT>::K][kPlanes],
                                        TileNode (&own)[TileGeom<TW, TH, NT>::K],
-                                       TileLDS<TW, TH> &L, unsigned &bad) {
+                                       TileLDS<TW, TH> &L, Health &health) {
   using G = TileGeom<TW, TH>;
 #pragma unroll
   for (int k = 0; k < S.K; ++k) {
@@ -179,31 +178,21 @@ __device__ __forceinline__ void tile_a(const DomainArgs &d, const TileSlots<TW, 
 #pragma unroll
     for (int q = 0; q < kQ; ++q) F[q] = ld[k][q];
     const real sv = ld[k][9];
-    const NodeMoments m = node_moments(F, d);
-    const real inv_rho = rcp_fast(m.rho);
-    const real ux = m.jx * inv_rho, uy = m.jy * inv_rho;
-    real th, lap_val;
-    if (d.flags & kFlagPreciseTheta) {
-      lap_val = node_dtheta(m.dr, m.rho, sv, d);
-      th = d.theta_ref + lap_val;
-    } else {
-      th = node_theta(m.rho, sv, d);
-      lap_val = th;
-    }
     const int ia = (S.py[k] + 2) * G::AW + (S.px[k] + 2);
-    L.ux[ia] = ux;
-    L.uy[ia] = uy;
-    L.lap[ia] = lap_val;
-    L.gx[ia] = m.rho * ux * ((real(1) - th) - ux * ux);
-    L.gy[ia] = m.rho * uy * ((real(1) - th) - uy * uy);
+    real gx, gy;
+    const NodeState o = node_state(d, F, sv, health, gx, gy);
+    L.ux[ia] = o.ux;
+    L.uy[ia] = o.uy;
+    L.lap[ia] = o.lapv;
+    L.gx[ia] = gx;
+    L.gy[ia] = gy;
     L.s[ia] = sv;
-    own[k] = TileNode{m.dr, m.rho, m.pxx, m.pyy, m.pxy, ux, uy, th, sv};
-    bad |= (m.rho > real(0) && th > real(0) && __builtin_isfinite(ux + uy + th)) ? 0u : 1u;
+    own[k] = o;
   }
 }
 
 // B: collision of the tile and the collision ring; the eight moving
-// populations into LDS, population 0 and Phi into registers.  y0: the
+// populations into LDS, population 0 and the heat into registers.  y0: the
 // tile's row origin (wall rows go by the unwrapped row index, as in the row
 // sweep).
 template <int TW, int TH, int NT>
@@ -211,104 +200,60 @@ __device__ __forceinline__ void tile_b(const DomainArgs &d, const int y0,
                                        const TileSlots<TW, TH, NT> &S,
                                        const TileNode (&own)[TileGeom<TW, TH, NT>::K],
                                        TileLDS<TW, TH> &L, real (&keep_f0)[TileGeom<TW, TH, NT>::K],
-                                       real (&keep_phi)[TileGeom<TW, TH, NT>::K]) {
+                                       real (&keep_heat)[TileGeom<TW, TH, NT>::K]) {
   using G = TileGeom<TW, TH>;
-  const real cs2 = real(kCs2);
-  const real cref = cs2 * (d.theta_ref - real(1));
 #pragma unroll
   for (int k = 0; k < S.K; ++k) {
     if (!S.coll[k]) continue;
-    const TileNode &o = own[k];
+    NodeState o = own[k];
     const int i = (S.py[k] + 2) * G::AW + (S.px[k] + 2);
-    const real rho = o.rho, ux = o.ux, uy = o.uy, th = o.th, dr = o.dr;
-    const real uxe = L.ux[i + 1], uxw = L.ux[i - 1];
-    const real uye = L.uy[i + 1], uyw = L.uy[i - 1];
-    const real uxn = L.ux[i + G::AW], uxs = L.ux[i - G::AW];
-    const real uyn = L.uy[i + G::AW], uys = L.uy[i - G::AW];
-    const real dxux = real(0.5) * (uxe - uxw), dxuy = real(0.5) * (uye - uyw);
-    const real dyux = real(0.5) * (uxn - uxs), dyuy = real(0.5) * (uyn - uys);
-    const real div = dxux + dyuy;
-    const real p = rho * cs2 * th;
-    const real dth = th - d.theta_ref;
-    const real dp = cs2 * (dr * th + d.rho_ref * dth);  // p - p_ref
-    const real tau = div_fast(d.mu, p);
-    const real taub = tau + real(0.5);
-    const real itaub = rcp_fast(taub);
-    const real gc = L.gx[i];
-    const real gxe = L.gx[i + 1], gxw = L.gx[i - 1];
-    const real gcy = L.gy[i];
-    const real gyn = L.gy[i + G::AW], gys = L.gy[i - G::AW];
-    real e1x, e1y;
-    if (d.flags & kFlagE1Centred) {
-      e1x = real(0.5) * (gxe - gxw);
-      e1y = real(0.5) * (gyn - gys);
-    } else {
-      const real ep = d.sgn_eps;
-      e1x = ux > ep ? gc - gxw : (ux < -ep ? gxe - gc : real(0.5) * (gxe - gxw));
-      e1y = uy > ep ? gcy - gys : (uy < -ep ? gyn - gcy : real(0.5) * (gyn - gys));
-    }
-    const real e2 = (d.flags & kFlagE2Off) ? real(0) : d.e2c * p * div;
-    const real Exx = e1x + e2, Eyy = e1y + e2;
-    const real rux = rho * ux, ruy = rho * uy;
-    const real ruxx = rux * ux, ruyy = ruy * uy, ruxy = rux * uy;
-    const real prxx = (o.pxx - dp) - ruxx + real(0.5) * Exx;
-    const real pryy = (o.pyy - dp) - ruyy + real(0.5) * Eyy;
-    const real prxy = o.pxy - ruxy;
-    const real tp = taub * p;
-    const real fdxx = -tp * (dxux - dyuy);
-    const real fdxy = -tp * (dyux + dxuy);
+    o.ux = L.ux[i];
+    o.uy = L.uy[i];
+    o.lapv = L.lap[i];
+    NodeStencil n;
+    n.uxe = L.ux[i + 1];
+    n.uxw = L.ux[i - 1];
+    n.uye = L.uy[i + 1];
+    n.uyw = L.uy[i - 1];
+    n.uxn = L.ux[i + G::AW];
+    n.uxs = L.ux[i - G::AW];
+    n.uyn = L.uy[i + G::AW];
+    n.uys = L.uy[i - G::AW];
+    n.gxe = L.gx[i + 1];
+    n.gxc = L.gx[i];
+    n.gyc = L.gy[i];
+    n.gxw = L.gx[i - 1];
+    n.gyn = L.gy[i + G::AW];
+    n.gys = L.gy[i - G::AW];
     const int yk = y0 + S.py[k];
     const bool wall_row = d.bcy == kBcWall && (yk == 0 || yk == d.ny - 1);
-    const real sg = wall_row ? real(1) : d.sigma, sg1 = real(1) - sg;
-    const real a1xx = sg * prxx + sg1 * fdxx;
-    const real a1yy = sg * pryy - sg1 * fdxx;
-    const real a1xy = sg * prxy + sg1 * fdxy;
-    const real c = cs2 * (th - real(1));
-    const real a1xxy = uy * a1xx + real(2) * ux * a1xy;
-    const real a1xyy = ux * a1yy + real(2) * uy * a1xy;
-    const real a1xxyy = real(2) * (ux * a1xyy + uy * a1xxy) + (c - ux * ux) * a1yy +
-                        (c - uy * uy) * a1xx - real(4) * ux * uy * a1xy;
-    const real om = real(1) - itaub;
-    const real drc = dp - cs2 * dr;
-    const real dc = cs2 * dth;
-    const real drc2 = dr * c * c + d.rho_ref * dc * (c + cref);
-    const real Axx = ruxx + drc + om * a1xx + real(0.5) * Exx;
-    const real Ayy = ruyy + drc + om * a1yy + real(0.5) * Eyy;
-    const real Axy = ruxy + om * a1xy;
-    const real rc = rho * c;
-    const real Axxy = ruxx * uy + rc * uy + om * a1xxy;
-    const real Axyy = ruyy * ux + rc * ux + om * a1xyy;
-    const real Axxyy = (d.flags & kFlagFeq3)
-                           ? real(0)
-                           : ruxx * uy * uy + rc * (ux * ux + uy * uy) + drc2 + om * a1xxyy;
-    real f[kQ];
-    project(dr, rux, ruy, Axx, Axy, Ayy, Axxy, Axyy, Axxyy, f);
+    real f[kQ], phi, pt;
+    collide(d, o, n, wall_row ? real(1) : d.sigma, wall_row ? real(0) : d.sigma1, f, phi, pt);
     const int j = (S.py[k] + 1) * G::BW + (S.px[k] + 1);
 #pragma unroll
     for (int q = 1; q < kQ; ++q) L.f[q - 1][j] = f[q];
-    real phi;
-    if (d.flags & kFlagPhiFD) {
-      const real aa = dxux - dyuy, bb = dyux + dxuy;
-      phi = d.mu * (aa * aa + bb * bb);
-    } else {
-      phi = -(tau * itaub) * (a1xx * dxux + a1xy * (dyux + dxuy) + a1yy * dyuy);
-    }
     keep_f0[k] = f[0];
-    keep_phi[k] = phi;
+    const real lap = laplacian(o.lapv, L.lap[i + 1], L.lap[i - 1], L.lap[i + G::AW],
+                               L.lap[i - G::AW]);
+    keep_heat[k] = heat_term(d, lap, phi, pt);
   }
+}
+
+// u ds/dx at node i along the axis of neighbour stride w.
+__device__ __forceinline__ real tile_muscl(real u, const real *s, const int i, const int w) {
+  return muscl(u, s[i - w] - s[i - 2 * w], s[i] - s[i - w], s[i + w] - s[i],
+               s[i + 2 * w] - s[i + w]);
 }
 
 // C of slot k (a tile node): the streamed populations and the new entropy.
 template <int TW, int TH, int NT>
-__device__ __forceinline__ void tile_c(const DomainArgs &d, const int k,
+__device__ __forceinline__ void tile_c(const int k,
                                        const TileSlots<TW, TH, NT> &S,
-                                       const TileNode (&own)[TileGeom<TW, TH, NT>::K],
                                        const TileLDS<TW, TH> &L,
                                        const real (&keep_f0)[TileGeom<TW, TH, NT>::K],
-                                       const real (&keep_phi)[TileGeom<TW, TH, NT>::K],
+                                       const real (&keep_heat)[TileGeom<TW, TH, NT>::K],
                                        real (&Fo)[kQ], real &snew) {
   using G = TileGeom<TW, TH>;
-  const TileNode &o = own[k];
   const int j = (S.py[k] + 1) * G::BW + (S.px[k] + 1);
   const int i = (S.py[k] + 2) * G::AW + (S.px[k] + 2);
   Fo[0] = keep_f0[k];
@@ -320,13 +265,8 @@ __device__ __forceinline__ void tile_c(const DomainArgs &d, const int k,
   Fo[4] = L.f[3][j + G::BW];           // from y + 1
   Fo[7] = L.f[6][j + G::BW + 1];       // from (x + 1, y + 1)
   Fo[8] = L.f[7][j + G::BW - 1];       // from (x - 1, y + 1)
-  const real sc = o.sv;
-  const real advx = muscl_term(o.ux, L.s[i - 2], L.s[i - 1], sc, L.s[i + 1], L.s[i + 2]);
-  const real advy = muscl_term(o.uy, L.s[i - 2 * G::AW], L.s[i - G::AW], sc, L.s[i + G::AW],
-                               L.s[i + 2 * G::AW]);
-  const real lap = ((L.lap[i + 1] + L.lap[i - 1]) + (L.lap[i + G::AW] + L.lap[i - G::AW])) -
-                   real(4) * L.lap[i];
-  snew = sc - (advx + advy) + div_fast(d.lambda * lap + keep_phi[k], o.rho * o.th);
+  snew = L.s[i] - (tile_muscl(L.ux[i], L.s, i, 1) + tile_muscl(L.uy[i], L.s, i, G::AW)) +
+         keep_heat[k];
 }
 
 // C of every tile slot, stored to the state at dst0 (tile origin x0, y0);
@@ -335,10 +275,9 @@ __device__ __forceinline__ void tile_c(const DomainArgs &d, const int k,
 template <int TW, int TH, int NT>
 __device__ __forceinline__ void tile_c_store(const DomainArgs &d, real *dst0, const int x0,
                                              const int y0, const TileSlots<TW, TH, NT> &S,
-                                             const TileNode (&own)[TileGeom<TW, TH, NT>::K],
                                              const TileLDS<TW, TH> &L,
                                              const real (&keep_f0)[TileGeom<TW, TH, NT>::K],
-                                             const real (&keep_phi)[TileGeom<TW, TH, NT>::K],
+                                             const real (&keep_heat)[TileGeom<TW, TH, NT>::K],
                                              real *mom, const long long mom_sc) {
   constexpr unsigned kEl = sizeof(real);
 #pragma unroll
@@ -347,7 +286,7 @@ __device__ __forceinline__ void tile_c_store(const DomainArgs &d, real *dst0, co
     const int x = x0 + S.px[k], y = y0 + S.py[k];
     if (x >= d.nx || y >= d.ny) continue;
     real Fo[kQ], snew;
-    tile_c<TW, TH>(d, k, S, own, L, keep_f0, keep_phi, Fo, snew);
+    tile_c<TW, TH>(k, S, L, keep_f0, keep_heat, Fo, snew);
     const unsigned off = (unsigned)(y * d.pitch + x) * kEl;
 #pragma unroll
     for (int q = 0; q < kQ; ++q) store_stream(dst0 + (long long)q * d.plane, off, Fo[q]);
@@ -394,15 +333,15 @@ __global__ __launch_bounds__(NT) void k_tile_batch(BatchArgs a) {
       tile_correct<TW, TH>(d, a, dm, corr_shift(ctot, (long long)d.nx * d.ny, a.cconserve), x0,
                            y0, S, ld);
     TileNode own[G::K];
-    unsigned bad = 0;
-    tile_a<TW, TH>(d, S, ld, own, L, bad);
+    Health health;
+    tile_a<TW, TH>(d, S, ld, own, L, health);
     __syncthreads();
-    real keep_f0[G::K], keep_phi[G::K];
-    tile_b<TW, TH>(d, y0, S, own, L, keep_f0, keep_phi);
+    real keep_f0[G::K], keep_heat[G::K];
+    tile_b<TW, TH>(d, y0, S, own, L, keep_f0, keep_heat);
     __syncthreads();
-    tile_c_store<TW, TH>(d, a.dst_buf + off, x0, y0, S, own, L, keep_f0, keep_phi,
+    tile_c_store<TW, TH>(d, a.dst_buf + off, x0, y0, S, L, keep_f0, keep_heat,
                          a.mom ? a.mom + a.foffs[dm] : nullptr, a.mom_sc);
-    if (bad) atomicOr(a.status + dm, 1u);
+    if (health.bad()) atomicOr(a.status + dm, 1u);
   }
 }
 
@@ -441,7 +380,7 @@ void k_tile_batch2(BatchArgs a) {
     const unsigned frozen = domain_frozen(a.status + dm);
     const int x0 = __builtin_amdgcn_readfirstlane(w.y) * TW;
     const int y0 = __builtin_amdgcn_readfirstlane(w.z) * TH;
-    unsigned bad = 0;
+    Health health;
     // ---------------- step one on the virtual tile
     real hand[G1::K][kPlanes];  // its results, by slot
     {
@@ -455,16 +394,16 @@ void k_tile_batch2(BatchArgs a) {
                                      corr_shift(ctot, (long long)d.nx * d.ny, a.cconserve),
                                      x0 - 2, y0 - 2, S1, ld);
       TileNode own[G1::K];
-      tile_a<TW + 4, TH + 4>(d, S1, ld, own, L.l1, bad);
+      tile_a<TW + 4, TH + 4>(d, S1, ld, own, L.l1, health);
       __syncthreads();
-      real keep_f0[G1::K], keep_phi[G1::K];
-      tile_b<TW + 4, TH + 4>(d, y0 - 2, S1, own, L.l1, keep_f0, keep_phi);
+      real keep_f0[G1::K], keep_heat[G1::K];
+      tile_b<TW + 4, TH + 4>(d, y0 - 2, S1, own, L.l1, keep_f0, keep_heat);
       __syncthreads();
 #pragma unroll
       for (int k = 0; k < G1::K; ++k) {
         if (!S1.tile[k]) continue;
         real Fo[kQ], snew;
-        tile_c<TW + 4, TH + 4>(d, k, S1, own, L.l1, keep_f0, keep_phi, Fo, snew);
+        tile_c<TW + 4, TH + 4>(k, S1, L.l1, keep_f0, keep_heat, Fo, snew);
 #pragma unroll
         for (int q = 0; q < kQ; ++q) hand[k][q] = Fo[q];
         hand[k][9] = snew;
@@ -490,14 +429,14 @@ void k_tile_batch2(BatchArgs a) {
     }
     __syncthreads();  // the hand-over is read before the second step's arrays overwrite it
     TileNode own2[G2::K];
-    tile_a<TW, TH>(d, S2, ld2, own2, L.l2, bad);
+    tile_a<TW, TH>(d, S2, ld2, own2, L.l2, health);
     __syncthreads();
-    real keep2_f0[G2::K], keep2_phi[G2::K];
-    tile_b<TW, TH>(d, y0, S2, own2, L.l2, keep2_f0, keep2_phi);
+    real keep2_f0[G2::K], keep2_heat[G2::K];
+    tile_b<TW, TH>(d, y0, S2, own2, L.l2, keep2_f0, keep2_heat);
     __syncthreads();
-    tile_c_store<TW, TH>(d, a.dst_buf + off, x0, y0, S2, own2, L.l2, keep2_f0, keep2_phi,
+    tile_c_store<TW, TH>(d, a.dst_buf + off, x0, y0, S2, L.l2, keep2_f0, keep2_heat,
                          a.mom ? a.mom + a.foffs[dm] : nullptr, a.mom_sc);
-    if (bad) atomicOr(a.status + dm, 1u);
+    if (health.bad()) atomicOr(a.status + dm, 1u);
   }
 }
 
