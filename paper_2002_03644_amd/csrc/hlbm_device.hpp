@@ -98,6 +98,18 @@ __device__ __forceinline__ int map_index(int v, int n, int bc) {
   return v < 0 ? 0 : (v >= n ? n - 1 : v);
 }
 
+// Rows of a sweep in order, as map_index maps them, without a division a row.
+struct RowWalk {
+  int v, r;  // virtual row, and its wrapped index (periodic axis)
+  __device__ __forceinline__ RowWalk(int v0, int n, int bc) : v(v0), r(map_index(v0, n, bc)) {}
+  __device__ __forceinline__ int next(int n, int bc) {  // this row's index; moves to the next row
+    const int now = bc == 0 ? r : (v < 0 ? 0 : (v >= n ? n - 1 : v));
+    ++v;
+    r = r + 1 >= n ? 0 : r + 1;
+    return now;
+  }
+};
+
 __device__ __forceinline__ float fma_r(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_r(double a, double b, double c) { return __builtin_fma(a, b, c); }
 __device__ __forceinline__ float min_r(float a, float b) { return __builtin_fminf(a, b); }
@@ -546,12 +558,12 @@ struct LevelRegs {
   real p_adv = 0, p_heat = 0, p_vy = 0, p_f0 = 0, p_f2 = 0, q_f2 = 0;
 };
 
-// A(j): moments of one node of row j from its nine populations and entropy.
+// A(j): moments of one node of row j from its nine populations and entropy;
+// z = j mod 2.
 template <int W>
 __device__ __forceinline__ void level_a(const DomainArgs &d, LevelRegs &g, LevelRings<W> &R,
-                                        const int j, const int ri, const real (&F)[kQ],
+                                        const int z, const int ri, const real (&F)[kQ],
                                         const real sv, Health &health) {
-  const int z = j & 1;
   real gx, gy;
   const NodeState o = node_state(d, F, sv, health, gx, gy);
   R.ux[z][ri] = o.ux;
@@ -590,12 +602,12 @@ __device__ __forceinline__ void level_a(const DomainArgs &d, LevelRegs &g, Level
   g.n_gy = gy;
 }
 
-// B(k): collision, heat and x advection of row k (row k + 1 was the last A).
+// B(k): collision, heat and x advection of row k (row k + 1 was the last A);
+// z = k mod 2, sc = k mod 3.
 template <int W>
 __device__ __forceinline__ void level_b(const DomainArgs &d, LevelRegs &g, LevelRings<W> &R,
-                                        const int k, const int ri, const real sg,
+                                        const int z, const int sc, const int ri, const real sg,
                                         const real sg1) {
-  const int z = k & 1, sc = k % 3;
   NodeStencil n;
   n.uxe = R.ux[z][ri + 1];
   n.uxw = R.ux[z][ri - 1];
@@ -638,11 +650,11 @@ __device__ __forceinline__ void level_b(const DomainArgs &d, LevelRegs &g, Level
 }
 
 // C(k): pull streaming of row k and its entropy update (row k + 1 was the
-// last B).
+// last B); z = k mod 2, pm = (k - 1) mod 3 (the slots of row k in f0 and of row
+// k - 1 in fp).
 template <int W>
-__device__ __forceinline__ void level_c(const LevelRegs &g, const LevelRings<W> &R, const int k,
-                                        const int ri, real (&Fo)[kQ], real &snew) {
-  const int z = k & 1, pm = (k + 2) % 3;  // slot of row k in f0, of row k - 1 in fp
+__device__ __forceinline__ void level_c(const LevelRegs &g, const LevelRings<W> &R, const int z,
+                                        const int pm, const int ri, real (&Fo)[kQ], real &snew) {
   Fo[0] = g.p_f0;                  // row k, this column
   Fo[1] = R.f0[z][0][ri - 1];
   Fo[3] = R.f0[z][1][ri + 1];
@@ -660,7 +672,6 @@ template <bool kValue>
 struct Flag {
   static constexpr bool value = kValue;
 };
-
 // Batched items: the skip of a frozen domain is decided once per item for
 // the whole workgroup (another workgroup can set the flag at any moment, and
 // waves that read it at different times would disagree and pair up barriers
@@ -708,38 +719,36 @@ __device__ __forceinline__ void sweep_tile(const DomainArgs &d, const real *src0
   Health health;
   LevelRegs g;
 
-  // 32-bit byte offset of virtual row j (x fastest) from the plane bases.
-  auto row_off = [&](int j) {
-    return (unsigned)(map_index(y0 - 2 + j, d.ny, d.bcy) * d.pitch + cx) * kEl;
-  };
   real ld[kPlanes];
-  auto load_row = [&](int j) {
-    const unsigned off = row_off(j);
+  auto load_row = [&](const int j) {  // virtual row j, at a 32-bit byte offset
+    const unsigned off = (unsigned)(map_index(y0 - 2 + j, d.ny, d.bcy) * d.pitch + cx) * kEl;
 #pragma unroll
     for (int q = 0; q < kPlanes; ++q) ld[q] = load_at(src[q], off);
   };
-  auto stage_a = [&](int j) {
+  auto stage_a = [&](const int z) {
     real F[kQ];
 #pragma unroll
     for (int q = 0; q < kQ; ++q) F[q] = ld[q];
-    level_a(d, g, R, j, ri, F, ld[9], health);
+    level_a(d, g, R, z, ri, F, ld[9], health);
   };
 
   // A(i + 1), B(i), a barrier, the loads of row i + 2 and (kOut) C(i - 1).  The
   // loads come before C's stores: a wait for them never waits for this row's
-  // stores as well.
+  // stores as well.  m = i mod 3, mp = (i + 1) mod 3.
+  int m = 0, mp = 1;
   auto row = [&](const int i, auto kOut) {
-    stage_a(i + 1);
+    const int z = i & 1;
+    stage_a(1 - z);
     // wall rows take the projected stress alone: their rebuilt populations
     // carry the wall's finite-difference stress
     const int yk = y0 - 2 + i;
     const bool wall_row = d.bcy == kBcWall && (yk == 0 || yk == d.ny - 1);
-    level_b(d, g, R, i, ri, wall_row ? real(1) : d.sigma, wall_row ? real(0) : d.sigma1);
+    level_b(d, g, R, z, m, ri, wall_row ? real(1) : d.sigma, wall_row ? real(0) : d.sigma1);
     __syncthreads();
     if (i + 2 <= nrow + 3) load_row(i + 2);
     if constexpr (kOut.value) {
       real Fo[kQ], snew;
-      level_c(g, R, i - 1, ri, Fo, snew);
+      level_c(g, R, 1 - z, mp, ri, Fo, snew);
       if (own_col) {
         const unsigned off = (unsigned)((y0 + i - 3) * d.pitch + vx) * kEl;
 #pragma unroll
@@ -747,6 +756,8 @@ __device__ __forceinline__ void sweep_tile(const DomainArgs &d, const real *src0
         store_stream(dst[9], off, snew);
       }
     }
+    m = mp;
+    mp = mp == 2 ? 0 : mp + 1;
     __syncthreads();
   };
 
@@ -761,7 +772,8 @@ __device__ __forceinline__ void sweep_tile(const DomainArgs &d, const real *src0
 
 // Whole-domain step: one workgroup per tile.
 template <int CW>
-__global__ __launch_bounds__(CW + 64) void k_step(StepArgs a) {
+__global__ __launch_bounds__(CW + 64) __attribute__((amdgpu_waves_per_eu(HLBM_IS_F32 ? 6 : 2)))
+void k_step(StepArgs a) {
   __shared__ LevelRings<CW + 4> R;
   int bid = blockIdx.x;
   const int nblk = a.nbx * a.nby;

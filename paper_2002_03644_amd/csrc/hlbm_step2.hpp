@@ -24,11 +24,24 @@
 // nine populations and the entropy of level n + 1 at the lane's own node)
 // feeds A2 in registers on the same lanes; B2 on 3..CW+4; C2 on the tile.
 // Iteration i runs A1(i + 1), B1(i) and C2(i - 4), a barrier, issues the loads
-// of row i + 2 and runs C1(i - 1) -> A2(i - 1) and B2(i - 2), and a second
+// of row i + 3 and runs C1(i - 1) -> A2(i - 1) and B2(i - 2), and a second
 // barrier: each half holds one stage of each kind, and each level keeps the
 // one-step sweep's order between its own stages, so its rings have the same
-// depths: 24 rows of CW + 8 per level, 36.9 KB at CW = 184, four workgroups
-// of three whole waves per compute unit.
+// depths: 22 rows of CW + 8 per level, 34.3 KB at CW = 184, four workgroups
+// of three whole waves per compute unit (155 registers, three waves per SIMD).
+//
+// Two rows of loads are in flight, in two register sets that alternate (the
+// loop is unrolled by two): with one, a row's loads had half an iteration, about
+// a microsecond, to arrive.  us per step with one -> two: 200^2 8.2 -> 7.1,
+// 500^2 11.1 -> 9.7, 900^2 16.3 -> 15.1, 1500 x 1100 23.1 -> 21.7 (each on its
+// best tile), 8192^2 647 -> 619.  The batch kernel keeps one row in flight: its
+// per-domain arguments leave no room (168 registers with spills; 16 x 1024^2
+// 1229 -> 1286 us for a data step).
+//
+// The stores are plain: a 184-column row's ends share cache lines with the
+// neighbouring tiles', which run beside it on the same XCD, and the L2 joins
+// the two halves; non-temporal stores wrote both partial lines to memory (8192^2
+// 686 -> 634 us per step without them).
 //
 // Boundaries: out-of-range columns and rows wrap.  A halo lane then computes
 // level n + 1 of the wrapped node from the wrapped stencil, bit for bit what
@@ -77,25 +90,27 @@ __device__ __forceinline__ void sweep_tile2(const DomainArgs &d, const real *src
   Health health, health2;
   LevelRegs g1, g2;
 
-  auto row_off = [&](int j) {
-    return (unsigned)(map_index(y0 - 4 + j, d.ny, d.bcy) * d.pitch + cx) * kEl;
-  };
-  real ld[kPlanes];
-  auto load_row = [&](int j) {
-    const unsigned off = row_off(j);
+  RowWalk walk(y0 - 4, d.ny, d.bcy);
+  // rows in flight: an even and an odd one (batch: one)
+  constexpr int kAhead = kBatch ? 1 : 2;
+  real lda[kPlanes], ldb[kPlanes];
+  auto load_row = [&](real (&to)[kPlanes]) {  // the next row
+    const unsigned off = (unsigned)(walk.next(d.ny, d.bcy) * d.pitch + cx) * kEl;
 #pragma unroll
-    for (int q = 0; q < kPlanes; ++q) ld[q] = load_at(src[q], off);
+    for (int q = 0; q < kPlanes; ++q) to[q] = load_at(src[q], off);
   };
-  auto stage_a1 = [&](int j) {
+  auto stage_a1 = [&](const int z, const real (&ld)[kPlanes]) {
     real F[kQ];
 #pragma unroll
     for (int q = 0; q < kQ; ++q) F[q] = ld[q];
-    level_a(d, g1, R.L1, j, ri, F, ld[9], health);
+    level_a(d, g1, R.L1, z, ri, F, ld[9], health);
   };
 
-  auto out_row = [&](const int k) {  // C2(k)
+  // Rows mod 3: m = i mod 3, mp = (i + 1) mod 3.
+  int m = 0, mp = 1;
+  auto out_row = [&](const int k, const int z) {  // C2(k)
     real Fo[kQ], snew;
-    level_c(g2, R.L2, k, ri, Fo, snew);
+    level_c(g2, R.L2, z, mp, ri, Fo, snew);
     if (c2) {
       const unsigned off = (unsigned)((y0 + k - 4) * d.pitch + vx) * kEl;
 #pragma unroll
@@ -103,38 +118,62 @@ __device__ __forceinline__ void sweep_tile2(const DomainArgs &d, const real *src
       store_at(dst[9], off, snew);
     }
   };
-  // A1(i + 1), B1(i), (kOut) C2(i - 4), a barrier, the loads of row i + 2,
-  // (kL2) C1(i - 1) -> A2(i - 1) and B2(i - 2), a barrier.
-  auto row = [&](const int i, auto kL2, auto kOut) {
-    stage_a1(i + 1);
-    level_b(d, g1, R.L1, i, ri, d.sigma, d.sigma1);
-    if constexpr (kOut.value) out_row(i - 4);
+  // A1(i + 1), B1(i), (kOut) C2(i - 4), a barrier, the loads of row i + 1 + kAhead,
+  // (kL2) C1(i - 1) -> A2(i - 1) and B2(i - 2), a barrier; z = i mod 2.
+  auto row = [&](const int i, const int z, real (&in)[kPlanes], auto kL2, auto kOut) {
+    stage_a1(1 - z, in);
+    level_b(d, g1, R.L1, z, m, ri, d.sigma, d.sigma1);
+    if constexpr (kOut.value) out_row(i - 4, z);
     __syncthreads();
-    if (i <= nrow + 5) load_row(i + 2);
+    if (i + 1 + kAhead <= nrow + 7) load_row(in);
     if constexpr (kL2.value) {
       real Fo[kQ], snew;
-      level_c(g1, R.L1, i - 1, ri, Fo, snew);
-      level_a(d, g2, R.L2, i - 1, ri, Fo, snew, health2);
-      level_b(d, g2, R.L2, i - 2, ri, d.sigma, d.sigma1);
+      level_c(g1, R.L1, 1 - z, mp, ri, Fo, snew);
+      level_a(d, g2, R.L2, 1 - z, ri, Fo, snew, health2);
+      level_b(d, g2, R.L2, z, mp, ri, d.sigma, d.sigma1);
     }
+    m = mp;
+    mp = mp == 2 ? 0 : mp + 1;
     __syncthreads();
   };
 
-  load_row(0);
-  stage_a1(0);
-  load_row(1);
+  load_row(lda);
+  if constexpr (kAhead == 2) load_row(ldb);
+  stage_a1(0, lda);
+  load_row(lda);
   if (barrier_skip<kBatch>(frozen)) return;
-  for (int i = 0; i < 3; ++i) row(i, Flag<false>(), Flag<false>());
-  for (int i = 3; i < 8; ++i) row(i, Flag<true>(), Flag<false>());
-  for (int i = 8; i <= nrow + 6; ++i) row(i, Flag<true>(), Flag<true>());
-  out_row(nrow + 3);
+  using No = Flag<false>;
+  using Yes = Flag<true>;
+  const int last = nrow + 6;
+  if constexpr (kBatch) {
+    for (int i = 0; i < 3; ++i) row(i, i & 1, lda, No(), No());
+    for (int i = 3; i < 8; ++i) row(i, i & 1, lda, Yes(), No());
+    for (int i = 8; i <= last; ++i) row(i, i & 1, lda, Yes(), Yes());
+  } else {
+    row(0, 0, ldb, No(), No());
+    row(1, 1, lda, No(), No());
+    row(2, 0, ldb, No(), No());
+    for (int i = 3; i < 7; i += 2) {
+      row(i, 1, lda, Yes(), No());
+      row(i + 1, 0, ldb, Yes(), No());
+    }
+    row(7, 1, lda, Yes(), No());
+    for (int i = 8; i <= last;) {  // (a strip of one row has none)
+      row(i, 0, ldb, Yes(), Yes());
+      if (++i > last) break;
+      row(i, 1, lda, Yes(), Yes());
+      ++i;
+    }
+  }
+  out_row(nrow + 3, (nrow + 1) & 1);
   if constexpr (kBatch) __syncthreads();  // the next item reuses the rings
   if (health.bad() || (c1 && health2.bad())) atomicOr(status, 1u);
 }
 
 // Two steps of a whole periodic domain: one workgroup per tile.
 template <int CW>
-__global__ __launch_bounds__(step2_threads(CW)) void k_step2(StepArgs a) {
+__global__ __launch_bounds__(step2_threads(CW))
+__attribute__((amdgpu_waves_per_eu(HLBM_IS_F32 ? 3 : 1))) void k_step2(StepArgs a) {
   __shared__ TileRings2<CW> R;
   int bid = blockIdx.x;
   const int nblk = a.nbx * a.nby;
@@ -150,7 +189,8 @@ __global__ __launch_bounds__(step2_threads(CW)) void k_step2(StepArgs a) {
 // Two steps of a batch of periodic domains: the persistent walk over (domain,
 // tile) items of the one-step batch kernel, with the two-step sweep.
 template <int CW>
-__global__ __launch_bounds__(step2_threads(CW)) void k_step_batch2(BatchArgs a) {
+__global__ __launch_bounds__(step2_threads(CW))
+__attribute__((amdgpu_waves_per_eu(HLBM_IS_F32 ? 3 : 1))) void k_step_batch2(BatchArgs a) {
   __shared__ TileRings2<CW> R;
   const TileWalk walk = tile_walk(a.nitems, a.xcd_walk);
   for (int it = walk.first; it < walk.end; it += walk.step) {
