@@ -80,7 +80,8 @@ typedef struct {
                            too with steps_per_launch = 2, whose workgroup is tile_w + 8
                            lanes rounded up to whole waves), 0 = auto */
   int32_t tile_h;       /* output rows per workgroup strip (>= 1), 0 = auto;
-                           hlbm_launch_shape reports what a step will use */
+                           hlbm_launch_shape reports the shape (with both
+                           automatic, the nominal one: see there) */
   double gamma;         /* heat-capacity ratio, > 1 */
   double prandtl;       /* Prandtl number, > 0; lambda = mu c_p / Pr */
   double mu;            /* dynamic viscosity, >= 0; local tau = mu / p */
@@ -144,8 +145,12 @@ int hlbm_validate(const hlbm_params *p);
  * strips at 192 columns in FP32, 32 otherwise, halved down to 4 rows until
  * about 768 workgroups exist in FP32 or 512 in FP64; never more rows than
  * ny.  Writes *host_tile_w and *host_tile_h; HLBM_OK, or HLBM_EINVAL if the
- * parameters are invalid or a pointer is NULL.  Host-only; callable without
- * a GPU. */
+ * parameters are invalid or a pointer is NULL.  These are the nominal shapes:
+ * with tile_w and tile_h both 0, hlbm_step fits width and height to whole
+ * rounds of the device's resident workgroups on grids of fewer than four such
+ * rounds, and there also takes FP32 domains periodic along both axes two steps
+ * at a time below 900,000 nodes unless steps_per_launch is 1 (results are the
+ * same bit for bit).  Host-only; callable without a GPU. */
 int hlbm_launch_shape(const hlbm_params *p, int32_t *host_tile_w, int32_t *host_tile_h);
 
 /* Launch plan of hlbm_step for these parameters: steps per kernel launch (1

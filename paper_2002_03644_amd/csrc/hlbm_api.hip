@@ -171,6 +171,22 @@ hipError_t apply_walls(hlbm_handle *h, void *state, hipStream_t st) {
                                 : hlbm::f32::wall(h->dom, state, st);
 }
 
+// Launches of hlbm_step: the nominal plan (what hlbm_launch_plan reports), with
+// what it leaves to the library fitted to the device (see fit_tile).  Small
+// grids that may take two steps per launch then do, also below
+// kTwoStepMinNodes: with fitted strips they are faster there too.
+void plan_launches(hlbm_handle *h) {
+  const hlbm_params *p = &h->p;
+  const int es = (int)elem_size(p->dtype);
+  h->tile = default_tile(p);
+  h->tile2 = default_tile2(p);
+  h->spl = steps_per_launch(p);
+  if (p->tile_w || p->tile_h) return;
+  h->spl = batch_steps_per_launch(p);
+  h->tile = hlbm::fit_tile(p->nx, p->ny, h->tile, es, 1);
+  if (h->spl == 2 && es == 4) h->tile2 = hlbm::fit_tile(p->nx, p->ny, h->tile2, es, 2);
+}
+
 hipError_t run_reduce(hlbm_handle *h, double host[hlbm::kReduceVals], hipStream_t st) {
   hipError_t e;
   const void *state = buf(h, h->cur);
@@ -279,9 +295,7 @@ int hlbm_init(hlbm_handle **out, const hlbm_params *p, void *workspace, size_t w
   h->ws = (char *)workspace;
   h->cur = 0;
   h->steps = 0;
-  h->tile = default_tile(p);
-  h->tile2 = default_tile2(p);
-  h->spl = steps_per_launch(p);
+  plan_launches(h);
   fill_domain(p, &h->dom);
   hipStream_t st = (hipStream_t)stream;
   hipError_t e;

@@ -103,6 +103,71 @@ inline TileShape step2_tile(int nx, int ny, int tile_w, int tile_h, int elem_siz
   return t;
 }
 
+// Tile shape that an automatic launch takes (tile_w and tile_h both left to
+// the library) in place of the nominal one above, on grids of a few rounds of
+// resident workgroups.  There the time is a whole number of rounds times the
+// sweep's iterations (output rows plus the fill of its pipeline), so a strip
+// height from a fixed list can leave the last round nearly empty: 1500 x 1100
+// in two-step strips of 184 x 8 is 1242 workgroups, a second round of 218.  The
+// shape is the one of least modelled time over all widths and heights: full
+// rounds at the resident load plus the rest at its own, each (rows + fill)
+// iterations of the time an iteration takes with that many waves per SIMD
+// (measured, in units of 10 ns; below about two waves it hardly rises, the
+// sweep then waits on its own latencies).  us per step, nominal -> fitted:
+// FP32 two-step 1500 x 1100 31.0 -> 21.7, 900^2 (one step before) 23.2 -> 15.1,
+// 500^2 11.8 -> 9.7, 200^2 9.9 -> 7.1, 2048^2 55.2 -> 50.4; one-step 2048 x 512
+// 26.8 -> 23.9; FP64 2048^2 199 -> 166.
+//
+// Grids of at least four full rounds of nominal tiles keep those: their rounds
+// even out and memory bounds them (8192^2: 64 rows 631 us per step, 48 644,
+// 96 697).
+struct FitShape {
+  int bw, waves, per_cu, max_nx;  // width, waves per workgroup, resident workgroups per CU
+};
+inline TileShape fit_tile(int nx, int ny, const TileShape &nominal, int elem_size, int steps) {
+  constexpr long long kCUs = 256;
+  static const FitShape two[] = {{64, 2, 6, 64}, {120, 2, 6, 1 << 30}, {184, 3, 4, 1 << 30}};
+  static const FitShape one32[] = {
+      {64, 2, 12, 1 << 30}, {128, 3, 8, 1 << 30}, {192, 4, 6, 1 << 30}, {256, 5, 4, 1 << 30}};
+  static const FitShape one64[] = {{64, 2, 4, 1 << 30}, {128, 3, 2, 1 << 30}, {192, 4, 2, 1 << 30}};
+  // time of an iteration by half waves per SIMD, from one half up
+  static const int t_two[] = {145, 173, 178, 186, 232, 240};
+  static const int t_one32[] = {115, 124, 140, 160, 182, 205, 225, 240, 260, 280, 305, 330};
+  static const int t_one64[] = {185, 215, 290, 325};
+  const FitShape *shapes = steps == 2 ? two : (elem_size == 4 ? one32 : one64);
+  const int count = steps == 2 ? 3 : (elem_size == 4 ? 4 : 3);
+  const int *time = steps == 2 ? t_two : (elem_size == 4 ? t_one32 : t_one64);
+  const int fill = steps == 2 ? 8 : 4;
+  auto tiles = [&](int bw, int rows) {
+    return (long long)((nx + bw - 1) / bw) * ((ny + rows - 1) / rows);
+  };
+  for (int k = 0; k < count; ++k)
+    if (shapes[k].bw == nominal.bw &&
+        tiles(nominal.bw, nominal.rows) >= 4 * kCUs * shapes[k].per_cu)
+      return nominal;
+  TileShape best = nominal;
+  long long least = -1;
+  for (int k = 0; k < count; ++k) {
+    const FitShape &f = shapes[k];
+    if (nx > f.max_nx) continue;
+    auto iter = [&](long long wgs_per_cu) {  // ceil(2 wgs waves / 4), as an index
+      return time[(wgs_per_cu * f.waves + 1) / 2 - 1];
+    };
+    for (int rows = ny < 2 ? ny : 2; rows <= ny && rows <= 128; ++rows) {
+      const long long nb = tiles(f.bw, rows), resident = kCUs * f.per_cu;
+      const long long rest = nb % resident;
+      const long long cost = (rows + fill) * ((nb / resident) * iter(f.per_cu) +
+                                              (rest ? iter((rest + kCUs - 1) / kCUs) : 0));
+      if (least < 0 || cost < least) {
+        least = cost;
+        best.bw = f.bw;
+        best.rows = rows;
+      }
+    }
+  }
+  return best;
+}
+
 // Elements from one state row to the next: nx rounded up to 64, so that every
 // row, and with it every tile's row segment, starts 256-byte aligned (FP32).
 // Rows of other widths lost 5 % (6000 and 14000 columns, rows 64-byte

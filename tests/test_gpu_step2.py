@@ -125,3 +125,21 @@ def test_two_step_conserves_mass_and_momentum():
     assert G.status()[0] == HLBM_OK
     for k in range(3):
         assert abs(t1[k] - t0[k]) / t0[0] < 1e-13
+
+
+@pytest.mark.parametrize("nx,ny,opts", [
+    (200, 200, {}), (64, 65, {}), (65, 1, {}), (121, 3, {}), (1500, 1100, {}), (185, 2049, {}),
+    (700, 33, dict(bc_x="extrapolate")), (2, 100, dict(bc_y="wall", wall_theta=0.2)),
+    (2048, 50, dict(bc_x="extrapolate", bc_y="extrapolate")),
+])
+@pytest.mark.parametrize("dt", ["f32", "f64"])
+def test_fitted_launches_equal_given_tiles(nx, ny, opts, dt):
+    """With the tile left to the library the launches are fitted to the device
+    (other widths and heights, two steps per launch on small FP32 grids); the
+    results are those of a given tile and one step per launch, bit for bit,
+    over an odd number of steps."""
+    f = hi.random_smooth(nx, ny, seed=nx + ny, amp=0.03, u0=(0.12, -0.08))
+    base = dict(dtype=dt, mu=2e-3, sigma=0.3, **opts)
+    auto = run(Params(nx, ny, **base), f, 5)
+    given = run(Params(nx, ny, tile_w=128, tile_h=8, steps_per_launch=1, **base), f, 5)
+    assert torch.equal(state(auto), state(given))
