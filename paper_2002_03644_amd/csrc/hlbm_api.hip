@@ -183,8 +183,11 @@ void plan_launches(hlbm_handle *h) {
   h->spl = steps_per_launch(p);
   if (p->tile_w || p->tile_h) return;
   h->spl = batch_steps_per_launch(p);
-  h->tile = hlbm::fit_tile(p->nx, p->ny, h->tile, es, 1);
-  if (h->spl == 2 && es == 4) h->tile2 = hlbm::fit_tile(p->nx, p->ny, h->tile2, es, 2);
+  if (h->spl == 2) {  // (its odd last step keeps the nominal one-step shape)
+    if (es == 4) h->tile2 = hlbm::fit_tile(p->nx, p->ny, h->tile2, es, 2);
+  } else {
+    h->tile = hlbm::fit_tile(p->nx, p->ny, h->tile, es, 1);
+  }
 }
 
 hipError_t run_reduce(hlbm_handle *h, double host[hlbm::kReduceVals], hipStream_t st) {

@@ -205,11 +205,101 @@ __device__ __forceinline__ float log_normal(float x) {
   const float r = y * hi;
   return r + fma_r(y, lo, fma_r(y, hi, -r));
 }
-__device__ __forceinline__ double log_normal(double x) { return log(x); }
+
+#if !HLBM_IS_F32
+// A double constant that the compiler cannot lift out of the row loop: there
+// the thirty constants of the two functions below would hold sixty vector
+// registers for the whole sweep.  `zero` is an opaque zero (see opaque_zero); the
+// constant is formed in scalar registers beside its use.
+__device__ __forceinline__ int opaque_zero() {
+  int zero;
+  asm volatile("s_mov_b32 %0, 0" : "=s"(zero));
+  return zero;
+}
+__device__ __forceinline__ double near_const(const double c, const int zero) {
+  const unsigned long long bits = __builtin_bit_cast(unsigned long long, c);
+  const unsigned hi = (unsigned)(bits >> 32) ^ (unsigned)zero;
+  return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | (unsigned)bits);
+}
+
+// a b + c with c = near_const(value): written out, as the compiler would copy
+// the constant to a vector register for its two-operand form first.
+__device__ __forceinline__ double fma_const(double a, double b, const double c, const int zero) {
+  double r;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(near_const(c, zero)));
+  return r;
+}
+
+// Their own logarithm and exponential take the FP64 sweep's node from about 110
+// to 60 instructions for theta, and without library constants held across the
+// row loop and the library's second, precise-theta branch it needs 153 vector
+// registers instead of 208: three waves per SIMD.  2048^2 164 -> 152 us per step,
+// Couette 2 x 100 15.6 -> 13.6; theta over rho = e^-8 .. e^8 is 10.5 units of 2^-53
+// off at most (14.4 before), 1.0 near rho = 1, s = 0 (1.0).
+//
+// ln x of a positive normal number, x = 2^k m with m in [sqrt(1/2), sqrt(2)):
+// k ln 2 + 2 atanh(t), t = (m - 1) / (m + 1), by the series of atanh to t^21 (|t| <
+// 0.172: truncated below 2^-56 of t).  Within 1.5 units in the last place.
+__device__ __forceinline__ double log_near(double x, const int zero) {
+  double m = __builtin_amdgcn_frexp_mant(x);  // [1/2, 1)
+  int k = __builtin_amdgcn_frexp_exp(x);
+  const bool low = m < 0.70710678118654752440;
+  m = low ? m + m : m;
+  k = low ? k - 1 : k;
+  const double f = m - 1.0, den = m + 1.0;
+  const double r = rcp_fast(den);
+  double t = f * r;
+  t = __builtin_fma(__builtin_fma(-t, den, f), r, t);
+  const double z = t * t;
+  double p = near_const(2.0 / 21.0, zero);
+  p = fma_const(p, z, 2.0 / 19.0, zero);
+  p = fma_const(p, z, 2.0 / 17.0, zero);
+  p = fma_const(p, z, 2.0 / 15.0, zero);
+  p = fma_const(p, z, 2.0 / 13.0, zero);
+  p = fma_const(p, z, 2.0 / 11.0, zero);
+  p = fma_const(p, z, 2.0 / 9.0, zero);
+  p = fma_const(p, z, 2.0 / 7.0, zero);
+  p = fma_const(p, z, 2.0 / 5.0, zero);
+  p = fma_const(p, z, 2.0 / 3.0, zero);
+  const double log_m = __builtin_fma(t * z, p, t + t);
+  return __builtin_fma((double)k, near_const(0.69314718055994530942, zero), log_m);
+}
+
+// e^x - off, off 0 or 1: 2^k + 2^k (e^r - 1) - off with k = round(x / ln 2), |r|
+// <= ln 2 / 2 in two parts of ln 2 and e^r - 1 by the Taylor series to r^13
+// (truncated below 2^-57), so off = 1 is accurate relative to itself (expm1).
+__device__ __forceinline__ double exp_near(double x, const double off, const int zero) {
+  const double k = __builtin_rint(x * near_const(1.44269504088896340736, zero));
+  // ln 2 = hi + lo, hi with 32 trailing zero bits, so k hi is exact
+  constexpr double hi = 0x1.62e42feep-1, lo = 0x1.a39ef35793c76p-33;
+  double r = __builtin_fma(-k, near_const(hi, zero), x);
+  r = __builtin_fma(-k, near_const(lo, zero), r);
+  double p = near_const(1.0 / 6227020800.0, zero);
+  p = fma_const(p, r, 1.0 / 479001600.0, zero);
+  p = fma_const(p, r, 1.0 / 39916800.0, zero);
+  p = fma_const(p, r, 1.0 / 3628800.0, zero);
+  p = fma_const(p, r, 1.0 / 362880.0, zero);
+  p = fma_const(p, r, 1.0 / 40320.0, zero);
+  p = fma_const(p, r, 1.0 / 5040.0, zero);
+  p = fma_const(p, r, 1.0 / 720.0, zero);
+  p = fma_const(p, r, 1.0 / 120.0, zero);
+  p = fma_const(p, r, 1.0 / 24.0, zero);
+  p = fma_const(p, r, 1.0 / 6.0, zero);
+  p = __builtin_fma(p, r, 0.5);
+  const double q = __builtin_fma(r * r, p, r);
+  const double scale = __builtin_amdgcn_ldexp(1.0, (int)k);
+  return __builtin_fma(scale, q, scale - off);
+}
+#endif
 
 // theta from the stored entropy (deviation form: ds = s - s_ref).
 __device__ __forceinline__ real node_theta(real rho, real sv, const DomainArgs &d) {
+#if HLBM_IS_F32
   return d.theta_ref * exp_r(sv * d.inv_cv + d.gm1 * (log_normal(rho) - d.log_rho_ref));
+#else  // theta_ref = 1, log_rho_ref = 0 here
+  const int zero = opaque_zero();
+  return exp_near(fma_r(sv, d.inv_cv, d.gm1 * log_near(rho, zero)), 0.0, zero);
+#endif
 }
 
 // theta - theta_ref with relative accuracy on the deviation itself:
@@ -220,11 +310,12 @@ __device__ __forceinline__ real node_theta(real rho, real sv, const DomainArgs &
 // differences between neighbours are a few 1e-6 of theta, which absolute
 // FP32 values would round to a few per cent.
 //
-// FP32 uses the hardware exp and log with the classic corrections that make
-// them accurate relative to small results: Goldberg's log1p(y) = ln(u) y /
-// (u - 1) with u = 1 + y, exact when u rounds to 1, and expm1 by its Taylor
-// series for |x| < 1/4, else Kahan's (u - 1) x / ln(u) with u = e^x.  FP64
-// uses the library functions.
+// FP64 takes exp_near with off = 1.  FP32 uses the hardware exp and log with the
+// classic corrections that make them accurate relative to small results:
+// Goldberg's log1p(y) = ln(u) y / (u - 1) with u = 1 + y, exact when u rounds to
+// 1, and expm1 by its Taylor series for |x| < 1/4, else Kahan's (u - 1) x / ln(u)
+// with u = e^x.
+#if HLBM_IS_F32
 __device__ __forceinline__ float log1p_fast(float y) {
   const float u = 1.0f + y;
   const float um1 = u - 1.0f;
@@ -245,10 +336,7 @@ __device__ __forceinline__ float expm1_fast(float x) {
 __device__ __forceinline__ float node_dtheta(float dr, float rho, float sv, const DomainArgs &d) {
   return d.theta_ref * expm1_fast(sv * d.inv_cv + d.gm1 * log1p_fast(dr / d.rho_ref));
 }
-__device__ __forceinline__ double node_dtheta(double dr, double rho, double sv,
-                                              const DomainArgs &d) {
-  return d.theta_ref * expm1(sv * d.inv_cv + d.gm1 * (log(rho) - d.log_rho_ref));
-}
+#endif
 
 // van Albada limited slope b phi(a/b), phi(r) = (r^2 + r)/(r^2 + 1), zero for
 // a b <= 0; written as a b (a + b)/(a^2 + b^2).  Differences so small that
@@ -315,12 +403,18 @@ __device__ __forceinline__ NodeState node_state(const DomainArgs &d, const real 
   o.ux = m.jx * inv_rho;
   o.uy = m.jy * inv_rho;
   real th;
+#if HLBM_IS_F32
   if (d.flags & kFlagPreciseTheta) {
     o.lapv = node_dtheta(m.dr, m.rho, sv, d);
     th = o.lapv + d.th_off;
   } else {
     th = o.lapv = node_theta(m.rho, sv, d);
   }
+#else
+  const int zero = opaque_zero();
+  o.lapv = exp_near(fma_r(sv, d.inv_cv, d.gm1 * log_near(m.rho, zero)), d.th_off, zero);
+  th = o.lapv + d.th_off;
+#endif
   const real omt = real(1) - th;
   gx = m.rho * o.ux * fma_r(-o.ux, o.ux, omt);
   gy = m.rho * o.uy * fma_r(-o.uy, o.uy, omt);
@@ -772,7 +866,7 @@ __device__ __forceinline__ void sweep_tile(const DomainArgs &d, const real *src0
 
 // Whole-domain step: one workgroup per tile.
 template <int CW>
-__global__ __launch_bounds__(CW + 64) __attribute__((amdgpu_waves_per_eu(HLBM_IS_F32 ? 6 : 2)))
+__global__ __launch_bounds__(CW + 64) __attribute__((amdgpu_waves_per_eu(HLBM_IS_F32 ? 6 : 3)))
 void k_step(StepArgs a) {
   __shared__ LevelRings<CW + 4> R;
   int bid = blockIdx.x;
@@ -836,7 +930,8 @@ __device__ __forceinline__ TileWalk tile_walk(const int n, const int xcd) {
 }
 
 template <int CW>
-__global__ __launch_bounds__(CW + 64) void k_step_batch(BatchArgs a) {
+__global__ __launch_bounds__(CW + 64) __attribute__((amdgpu_waves_per_eu(HLBM_IS_F32 ? 4 : 3)))
+void k_step_batch(BatchArgs a) {
   __shared__ LevelRings<CW + 4> R;
   const TileWalk walk = tile_walk(a.nitems, a.xcd_walk);
   for (int it = walk.first; it < walk.end; it += walk.step) {

@@ -116,7 +116,7 @@ inline TileShape step2_tile(int nx, int ny, int tile_w, int tile_h, int elem_siz
 // sweep then waits on its own latencies).  us per step, nominal -> fitted:
 // FP32 two-step 1500 x 1100 31.0 -> 21.7, 900^2 (one step before) 23.2 -> 15.1,
 // 500^2 11.8 -> 9.7, 200^2 9.9 -> 7.1, 2048^2 55.2 -> 50.4; one-step 2048 x 512
-// 26.8 -> 23.9; FP64 2048^2 199 -> 166.
+// 26.8 -> 23.9; FP64 600^2 25.8 -> 23.7, 200^2 13.9 -> 11.4.
 //
 // Grids of at least four full rounds of nominal tiles keep those: their rounds
 // even out and memory bounds them (8192^2: 64 rows 631 us per step, 48 644,
@@ -129,11 +129,11 @@ inline TileShape fit_tile(int nx, int ny, const TileShape &nominal, int elem_siz
   static const FitShape two[] = {{64, 2, 6, 64}, {120, 2, 6, 1 << 30}, {184, 3, 4, 1 << 30}};
   static const FitShape one32[] = {
       {64, 2, 12, 1 << 30}, {128, 3, 8, 1 << 30}, {192, 4, 6, 1 << 30}, {256, 5, 4, 1 << 30}};
-  static const FitShape one64[] = {{64, 2, 4, 1 << 30}, {128, 3, 2, 1 << 30}, {192, 4, 2, 1 << 30}};
+  static const FitShape one64[] = {{64, 2, 6, 1 << 30}, {128, 3, 4, 1 << 30}, {192, 4, 3, 1 << 30}};
   // time of an iteration by half waves per SIMD, from one half up
   static const int t_two[] = {145, 173, 178, 186, 232, 240};
   static const int t_one32[] = {115, 124, 140, 160, 182, 205, 225, 240, 260, 280, 305, 330};
-  static const int t_one64[] = {185, 215, 290, 325};
+  static const int t_one64[] = {185, 190, 257, 285, 330, 400};
   const FitShape *shapes = steps == 2 ? two : (elem_size == 4 ? one32 : one64);
   const int count = steps == 2 ? 3 : (elem_size == 4 ? 4 : 3);
   const int *time = steps == 2 ? t_two : (elem_size == 4 ? t_one32 : t_one64);
@@ -150,14 +150,17 @@ inline TileShape fit_tile(int nx, int ny, const TileShape &nominal, int elem_siz
   for (int k = 0; k < count; ++k) {
     const FitShape &f = shapes[k];
     if (nx > f.max_nx) continue;
-    auto iter = [&](long long wgs_per_cu) {  // ceil(2 wgs waves / 4), as an index
+    const int nbx = (nx + f.bw - 1) / f.bw, resident = (int)kCUs * f.per_cu;
+    auto iter = [&](int wgs_per_cu) {  // ceil(2 wgs waves / 4), as an index
       return time[(wgs_per_cu * f.waves + 1) / 2 - 1];
     };
-    for (int rows = ny < 2 ? ny : 2; rows <= ny && rows <= 128; ++rows) {
-      const long long nb = tiles(f.bw, rows), resident = kCUs * f.per_cu;
-      const long long rest = nb % resident;
-      const long long cost = (rows + fill) * ((nb / resident) * iter(f.per_cu) +
-                                              (rest ? iter((rest + kCUs - 1) / kCUs) : 0));
+    for (int rows = ny < 2 ? ny : 2; rows <= ny && rows <= 128; rows += rows < 48 ? 1 : 4) {
+      const long long all = (long long)nbx * ((ny + rows - 1) / rows);
+      if (all > (1 << 24)) continue;
+      const int nb = (int)all, rounds = nb / resident, rest = nb - rounds * resident;
+      const long long cost =
+          (long long)(rows + fill) * (rounds * iter(f.per_cu) +
+                                      (rest ? iter((rest + (int)kCUs - 1) / (int)kCUs) : 0));
       if (least < 0 || cost < least) {
         least = cost;
         best.bw = f.bw;
