@@ -20,17 +20,25 @@ constexpr int kConvWaves = 4;   // waves per convolution workgroup
 
 size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-int wgrad_rows(int B, int H, int W) {
+// Rows per wave of a weight-gradient kernel: a divisor of H (a multiple of 4),
+// halved until there are `want` waves.  Layer 2 (256 registers) has two waves per
+// SIMD, 2048 on the chip; the others are bound by their reads, which more waves
+// keep in flight.
+constexpr int kWantHH = 2048, kWantHN = 4096;
+int wgrad_rows(int B, int H, int W, int want) {
   int rw = 64;
-  while (rw > kWgTR && (H % rw != 0 || (long long)B * (W / 32) * (H / rw) < 1024)) rw /= 2;
+  while (rw > 4 && (H % rw != 0 || (long long)B * (W / 32) * (H / rw) < want)) rw /= 2;
   return rw;
 }
 
-long long wgrad_parts(int B, int H, int W) {
-  return (long long)B * (W / 32) * (H / wgrad_rows(B, H, W));
+// workgroups (partials) of a layer
+long long wgrad_parts(int B, int H, int W, int want) {
+  const long long units = (long long)B * (W / 32) * (H / wgrad_rows(B, H, W, want));
+  return (units + kWgWaves - 1) / kWgWaves;
 }
 
-constexpr int kPartFloats = 9 * kHid * kHid + kHid;   // largest layer partial
+constexpr int kPart1 = 9 * kIn * kHid + kHid, kPart2 = 9 * kHid * kHid + kHid,
+              kPart3 = 9 * kHid * kOut + kOut;  // floats of a layer's partial
 
 }  // namespace
 
@@ -41,7 +49,8 @@ struct hlbm_cnn {
   float *params = nullptr, *grads = nullptr, *m = nullptr, *v = nullptr;
   bf16 *packed = nullptr;
   bf16 *xn = nullptr, *a1 = nullptr, *a2 = nullptr, *g3 = nullptr, *g2 = nullptr, *g1 = nullptr;
-  float *y = nullptr, *io_x = nullptr, *io_d = nullptr, *wpart = nullptr, *wcol = nullptr;
+  float *y = nullptr, *io_x = nullptr, *io_d = nullptr;
+  float *wpart[3] = {nullptr, nullptr, nullptr};  // weight-gradient partials by layer
   double *lpart = nullptr;
   size_t total = 0;
   float norm[16];
@@ -61,8 +70,11 @@ void layout(hlbm_cnn *c, char *base) {
     return p;
   };
   const size_t px = (size_t)c->maxb * c->npix;
-  long long parts = 0;
-  for (int b = 1; b <= c->maxb; ++b) parts = std::max(parts, wgrad_parts(b, c->H, c->W));
+  long long hh = 0, hn = 0;
+  for (int b = 1; b <= c->maxb; ++b) {
+    hh = std::max(hh, wgrad_parts(b, c->H, c->W, kWantHH));
+    hn = std::max(hn, wgrad_parts(b, c->H, c->W, kWantHN));
+  }
   c->params = (float *)take(sizeof(float) * kParams);
   c->grads = (float *)take(sizeof(float) * kParams);
   c->m = (float *)take(sizeof(float) * kParams);
@@ -75,8 +87,9 @@ void layout(hlbm_cnn *c, char *base) {
   c->g3 = (bf16 *)take(sizeof(bf16) * 4 * px);
   c->g2 = (bf16 *)take(sizeof(bf16) * kHid * px);
   c->g1 = (bf16 *)take(sizeof(bf16) * kHid * px);
-  c->wpart = (float *)take(sizeof(float) * kPartFloats * (size_t)parts);
-  c->wcol = (float *)take(sizeof(float) * kPartFloats * (size_t)kWgGroups);
+  c->wpart[0] = (float *)take(sizeof(float) * kPart1 * (size_t)hn);
+  c->wpart[1] = (float *)take(sizeof(float) * kPart2 * (size_t)hh);
+  c->wpart[2] = (float *)take(sizeof(float) * kPart3 * (size_t)hn);
   c->lpart = (double *)take(sizeof(double) * kLossParts + sizeof(float));
   c->io_x = (float *)take(sizeof(float) * 4 * px);
   c->io_d = (float *)take(sizeof(float) * 4 * px);
@@ -146,25 +159,43 @@ hipError_t conv(hlbm_cnn *c, int B, const bf16 *in, int pk, const float *bias, c
   return hipGetLastError();
 }
 
-template <int CIN, int COUT>
-hipError_t wgrad(hlbm_cnn *c, int B, const bf16 *in, const bf16 *g, int off, hipStream_t st) {
+// Weight-gradient partials of layer 1, 2 or 3 (summed by wgrad_reduce).
+hipError_t wgrad(hlbm_cnn *c, int B, int layer, const bf16 *in, const bf16 *g, hipStream_t st) {
+  const int want = layer == 2 ? kWantHH : kWantHN;
   WgradArgs a;
   a.in = in;
   a.grad = g;
-  a.partials = c->wpart;
+  a.partials = c->wpart[layer - 1];
   a.B = B;
   a.H = c->H;
   a.W = c->W;
-  a.rw = wgrad_rows(B, c->H, c->W);
+  a.rows = wgrad_rows(B, c->H, c->W, want);
   a.nsx = c->W / 32;
-  a.nry = c->H / a.rw;
-  const int parts = B * a.nsx * a.nry;
-  hipLaunchKernelGGL((k_wgrad<CIN, COUT>), dim3(parts), dim3(192), 0, st, a);
-  constexpr int P = 9 * CIN * COUT + COUT;
-  hipLaunchKernelGGL(k_wgrad_reduce, dim3((P + 255) / 256, kWgGroups), dim3(256), 0, st,
-                     (const float *)c->wpart, parts, P, c->wcol);
-  hipLaunchKernelGGL(k_wgrad_final, dim3((P + 255) / 256), dim3(256), 0, st,
-                     (const float *)c->wcol, P, c->grads + off);
+  a.nry = c->H / a.rows;
+  const dim3 grid((unsigned)wgrad_parts(B, c->H, c->W, want)), block(64 * kWgWaves);
+  if (layer == 1)
+    hipLaunchKernelGGL(k_wgrad_hn<true>, grid, block, 0, st, a);
+  else if (layer == 2)
+    hipLaunchKernelGGL(k_wgrad_hh, grid, block, 0, st, a);
+  else
+    hipLaunchKernelGGL(k_wgrad_hn<false>, grid, block, 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t wgrad_reduce(hlbm_cnn *c, int B, hipStream_t st) {
+  WgReduceArgs a;
+  const int size[3] = {kPart1, kPart2, kPart3}, dst[3] = {kOffW1, kOffW2, kOffW3};
+  int blocks = 0;
+  for (int l = 0; l < 3; ++l) {
+    a.partials[l] = c->wpart[l];
+    a.parts[l] = (int)wgrad_parts(B, c->H, c->W, l == 1 ? kWantHH : kWantHN);
+    a.size[l] = size[l];
+    a.dst[l] = dst[l];
+    a.first[l] = blocks;
+    blocks += (size[l] + 63) / 64;
+  }
+  a.grads = c->grads;
+  hipLaunchKernelGGL(k_wgrad_reduce, dim3(blocks), dim3(64 * kWgReduceWaves), 0, st, a);
   return hipGetLastError();
 }
 
@@ -396,15 +427,16 @@ int hlbm_cnn_loss_grad(hlbm_cnn *c, const float *x, int64_t x_sstride, int64_t x
                        1.0 / nel, loss);
   e = hipGetLastError();
   // layer 3: weights from (a2, g3); back to layer 2 through the ReLU of a2
-  if (e == hipSuccess) e = wgrad<kHid, kOut>(c, B, c->a2, c->g3, kOffW3, st);
+  if (e == hipSuccess) e = wgrad(c, B, 3, c->a2, c->g3, st);
   if (e == hipSuccess)
     e = conv<kOut, 2, kEpiMask>(c, B, c->g3, kPk3T, nullptr, c->a2, c->g2, nullptr, 0, 0, st);
   // layer 2: weights from (a1, g2); back to layer 1 through the ReLU of a1
-  if (e == hipSuccess) e = wgrad<kHid, kHid>(c, B, c->a1, c->g2, kOffW2, st);
+  if (e == hipSuccess) e = wgrad(c, B, 2, c->a1, c->g2, st);
   if (e == hipSuccess)
     e = conv<kHid, 2, kEpiMask>(c, B, c->g2, kPk2T, nullptr, c->a1, c->g1, nullptr, 0, 0, st);
   // layer 1: weights from (xn, g1)
-  if (e == hipSuccess) e = wgrad<kIn, kHid>(c, B, c->xn, c->g1, kOffW1, st);
+  if (e == hipSuccess) e = wgrad(c, B, 1, c->xn, c->g1, st);
+  if (e == hipSuccess) e = wgrad_reduce(c, B, st);
   return hip_status(e);
 }
 

@@ -535,179 +535,340 @@ void k_cnn_fused(FusedArgs a) {
 }
 
 // ---------------------------------------------------------- weight gradient
-// dW[t][ci][co] = sum_p in[p + off(t)][ci] g[p][co], db[co] = sum_p g[p][co]
-// over one workgroup's 32-pixel wide, `rw`-row tall patch, written as one
-// partial per workgroup.  Pixels run along K, so the patch is staged in LDS
-// channel-major: g as [co][row][32], the input as three copies shifted by
-// dx = -1, 0, +1, [dx][ci][row][32], which makes every fragment one aligned
-// 16-byte LDS read.  Wave w owns the taps of row offset dy = w.
-constexpr int kWgTR = 4;   // rows per LDS stage
+// dW[t][ci][co] = sum_p in[p + off(t)][ci] g[p][co], db[co] = sum_p g[p][co]:
+// matrix products with the pixels along K.  A fragment needs 8 consecutive
+// pixels of one channel where the tensors hold the channels of a pixel together:
+// a row segment is staged in LDS as it is (NHWC, 16-byte accesses) and read with
+// ds_read_b64_tr_b16, which hands lane j of each 16 lanes element j & 3 of the
+// 8-byte words of lanes (j >> 2), 4 + (j >> 2), 8 + ..., 12 + ...: with lane 4 e +
+// q addressing channels 4 q .. 4 q + 3 of pixel e, lane j receives channel j of
+// four consecutive pixels.  At 32 x 256^2, us: layer 2 63 (268 MB read, 4.3 TB/s),
+// layer 3 25 and layer 1 27 (151 MB, 5.6 to 6 TB/s); transposing by 2-byte LDS
+// writes, three shifted copies of the input each, took 239, 146 and 79.
+//
+// A wave owns a 32-pixel wide strip of `rows` rows and all taps; it stages, reads
+// and multiplies on its own, without barriers, with the next row's global loads
+// in flight.  The four waves of a workgroup then add their sums through LDS in a
+// fixed order and write one partial.
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+
+// Two 8-byte transposed reads: pixels 8 g .. 8 g + 7 of this lane's channel.  p:
+// the lane's own word of the first four pixels; step: bytes from there to that of
+// the second four.
+__device__ __forceinline__ bf16x8 read_tr(const char *p, const int step) {
+  typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)p);
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + step));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+__device__ __forceinline__ bf16x8 ones_frag() {
+  const bf16 o = (bf16)1.f;
+  return bf16x8{o, o, o, o, o, o, o, o};
+}
+
+constexpr int kWgWaves = 4;      // waves of a weight-gradient workgroup
+constexpr int kWgPix = 2 * kHid;  // bytes of a 32-channel pixel
+constexpr int kWgWide = 32 * kWgPix;         // staged row of a 32-channel tensor
+constexpr int kWgWideHalo = 34 * kWgPix;     // with the two halo pixels
+constexpr int kWgNarrowHalo = 34 * 2 * kIn;  // staged row of a 4-channel tensor with them
 
 struct WgradArgs {
-  const bf16 *in;     // layer input, NHWC CIN
-  const bf16 *grad;   // gradient of the layer output (pre-activation), NHWC COUT
-  float *partials;    // [workgroups][9 CIN COUT + COUT]
-  int B, H, W, rw, nsx, nry;
+  const bf16 *in;     // layer input, NHWC
+  const bf16 *grad;   // gradient of the layer output (pre-activation), NHWC
+  float *partials;    // [workgroups][P]
+  int B, H, W, rows, nsx, nry;
 };
 
-template <int CIN, int COUT>
-__global__ __launch_bounds__(192) void k_wgrad(WgradArgs a) {
-  constexpr int TR = kWgTR;
-  constexpr int CB = (COUT + 15) / 16, IB = (CIN + 15) / 16;
-  constexpr int GV = COUT >= 8 ? 8 : 4, IV = CIN >= 8 ? 8 : 4;   // channels per vector load
-  __shared__ __attribute__((aligned(16))) bf16 gt[COUT * TR * 32];
-  __shared__ __attribute__((aligned(16))) bf16 at[3 * CIN * (TR + 2) * 32];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int unit = blockIdx.x;
-  const int sx = unit % a.nsx;
-  const int rest = unit / a.nsx;
-  const int ry = rest % a.nry, b = rest / a.nry;
-  const int x0 = sx * 32, y0 = ry * a.rw;
-  const int W = a.W, H = a.H;
-  const long long img = (long long)b * H;
-  const int m = lane & 15, g = lane >> 4;
+// Unit (strip) of this wave, clamped: waves past the last one do the last
+// unit's loads and add nothing.
+struct WgUnit {
+  int x0, y0, b;
+  bool live;
+};
+__device__ __forceinline__ WgUnit wg_unit(const WgradArgs &a, const int wave) {
+  const int units = a.B * a.nsx * a.nry;
+  int u = blockIdx.x * kWgWaves + wave;
+  WgUnit w;
+  w.live = u < units;
+  u = w.live ? u : units - 1;
+  w.x0 = (u % a.nsx) * 32;
+  u /= a.nsx;
+  w.y0 = (u % a.nry) * a.rows;
+  w.b = u / a.nry;
+  return w;
+}
 
-  f32x4 acc[3][CB][IB];
+// Sum of the four waves' accumulators, in the order ((0 + 1) + (2 + 3)): waves 1
+// and 3 hand theirs over, then wave 2; on return wave 0 has the total.  S: NT
+// fragments of 64 lanes for each of two hand-overs.
+template <int NT>
+__device__ __forceinline__ void wg_sum(f32x4 (&acc)[NT], f32x4 *S, const int wave,
+                                       const int lane) {
+  __syncthreads();
+  f32x4 *mine = S + (wave >> 1) * NT * 64 + lane;
+  if (wave & 1) {
 #pragma unroll
-  for (int dx = 0; dx < 3; ++dx)
+    for (int k = 0; k < NT; ++k) mine[k * 64] = acc[k];
+  }
+  __syncthreads();
+  if (!(wave & 1)) {
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
+    for (int k = 0; k < NT; ++k) acc[k] += mine[k * 64];
+    if (wave == 2) {
 #pragma unroll
-      for (int ib = 0; ib < IB; ++ib) acc[dx][cb][ib] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float dbacc[CB];
-#pragma unroll
-  for (int cb = 0; cb < CB; ++cb) dbacc[cb] = 0.f;
-
-  for (int r0 = y0; r0 < y0 + a.rw; r0 += TR) {
-    __syncthreads();
-    // stage g rows r0 .. r0+TR-1
-    for (int it = tid; it < TR * 32 * (COUT / GV); it += 192) {
-      const int gi = it % (COUT / GV);
-      const int px = it / (COUT / GV);
-      const int x = px & 31, rr = px >> 5;
-      const bf16 *src = a.grad + ((img + r0 + rr) * W + x0 + x) * COUT + gi * GV;
-      if constexpr (GV == 8) {
-        const bf16x8 v = *(const bf16x8 *)src;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) gt[((gi * 8 + e) * TR + rr) * 32 + x] = v[e];
-      } else {
-        const bf16x4 v = *(const bf16x4 *)src;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) gt[((gi * 4 + e) * TR + rr) * 32 + x] = v[e];
-      }
-    }
-    // stage input rows r0-1 .. r0+TR, columns x0-1 .. x0+32
-    for (int it = tid; it < (TR + 2) * 34 * (CIN / IV); it += 192) {
-      const int gi = it % (CIN / IV);
-      const int px = it / (CIN / IV);
-      const int xp = px % 34, rr = px / 34;
-      const int yy = wrap(r0 - 1 + rr, H), xx = wrap(x0 - 1 + xp, W);
-      const bf16 *src = a.in + ((img + yy) * W + xx) * CIN + gi * IV;
-      bf16 v[IV];
-      if constexpr (IV == 8) {
-        const bf16x8 t = *(const bf16x8 *)src;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = t[e];
-      } else {
-        const bf16x4 t = *(const bf16x4 *)src;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = t[e];
-      }
-#pragma unroll
-      for (int dx = 0; dx < 3; ++dx) {
-        const int x = xp - dx;
-        if (x >= 0 && x < 32) {
-#pragma unroll
-          for (int e = 0; e < IV; ++e)
-            at[((dx * CIN + gi * IV + e) * (TR + 2) + rr) * 32 + x] = v[e];
-        }
-      }
-    }
-    __syncthreads();
-#pragma unroll 1
-    for (int rr = 0; rr < TR; ++rr) {
-      bf16x8 gf[CB];
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb) {
-        const int co = 16 * cb + m;
-        gf[cb] = co < COUT ? *(const bf16x8 *)&gt[(co * TR + rr) * 32 + 8 * g] : bf16x8{};
-      }
-      if (w == 0) {
-#pragma unroll
-        for (int cb = 0; cb < CB; ++cb)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) dbacc[cb] += (float)gf[cb][e];
-      }
-#pragma unroll
-      for (int dx = 0; dx < 3; ++dx) {
-#pragma unroll
-        for (int ib = 0; ib < IB; ++ib) {
-          const int ci = 16 * ib + m;
-          const bf16x8 bfr = ci < CIN
-              ? *(const bf16x8 *)&at[((dx * CIN + ci) * (TR + 2) + rr + w) * 32 + 8 * g]
-              : bf16x8{};
-#pragma unroll
-          for (int cb = 0; cb < CB; ++cb) acc[dx][cb][ib] = mfma(gf[cb], bfr, acc[dx][cb][ib]);
-        }
-      }
+      for (int k = 0; k < NT; ++k) mine[k * 64] = acc[k];
     }
   }
-  constexpr int P = 9 * CIN * COUT + COUT;
-  float *out = a.partials + (size_t)unit * P;
-  // D[m = co][n = ci]: lane n + 16 q, register r -> co = 16 cb + 4 q + r, ci = 16 ib + n
+  __syncthreads();
+  if (wave == 0) {
 #pragma unroll
-  for (int dx = 0; dx < 3; ++dx)
+    for (int k = 0; k < NT; ++k) acc[k] += S[NT * 64 + k * 64 + lane];
+  }
+}
+
+// Layer 2, 32 -> 32 channels: 36 products a row (nine taps, 2 x 2 blocks of 16
+// channels).  Input row y meets the gradient rows y + 1, y, y - 1 (taps dy = 0, 1,
+// 2), whose fragments are kept; rows outside the strip are zero.
+__global__ __launch_bounds__(64 * kWgWaves) __attribute__((amdgpu_waves_per_eu(2)))
+void k_wgrad_hh(WgradArgs a) {
+  constexpr int NT = 38;  // 36 weight blocks, 2 bias blocks
+  union Shared {
+    char stage[kWgWaves][kWgWideHalo + kWgWide];
+    f32x4 sum[2][NT][64];
+  };
+  __shared__ __attribute__((aligned(16))) Shared L;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const WgUnit u = wg_unit(a, wave);
+  const int W = a.W, H = a.H;
+  const long long img = (long long)u.b * H;
+  char *const sin = L.stage[wave];              // slot 0: pixel x0 - 1
+  char *const sg = L.stage[wave] + kWgWideHalo;
+  // this lane's word of a fragment's first four pixels
+  const int g = lane >> 4, e = (lane >> 2) & 3, q = lane & 3;
+  const int word = (8 * g + e) * kWgPix + 8 * q;
+  // halo pixels: lanes 0..3 pixel x0 - 1, lanes 4..7 pixel x0 + 32, 16 bytes each
+  const int hx = wrap(lane < 4 ? u.x0 - 1 : u.x0 + 32, W);
+  const int hslot = (lane < 4 ? 0 : 33) * kWgPix + (lane & 3) * 16;
+
+  bf16x8 li[2], lh = {}, lg[2];
+  auto load = [&](const int y) {  // input row y and gradient row y + 1
+    const char *row = (const char *)(a.in + (img + wrap(y, H)) * W * (long long)kHid);
+    const char *p = row + u.x0 * kWgPix + lane * 16;
+    li[0] = *(const bf16x8 *)p;
+    li[1] = *(const bf16x8 *)(p + 1024);
+    if (lane < 8) lh = *(const bf16x8 *)(row + hx * kWgPix + (lane & 3) * 16);
+    const char *gr = (const char *)(a.grad + (img + wrap(y + 1, H)) * W * (long long)kHid) +
+                     u.x0 * kWgPix + lane * 16;
+    lg[0] = *(const bf16x8 *)gr;
+    lg[1] = *(const bf16x8 *)(gr + 1024);
+  };
+  f32x4 acc[NT];
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb)
+  for (int k = 0; k < NT; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 gf[3][2] = {};  // gradient rows y - 1, y, y + 1
+  const bf16x8 one = ones_frag();
+  load(u.y0 - 1);
+  for (int i = -1; i <= a.rows; ++i) {
+    const int y = u.y0 + i;
+    *(bf16x8 *)(sin + kWgPix + lane * 16) = li[0];
+    *(bf16x8 *)(sin + kWgPix + 1024 + lane * 16) = li[1];
+    if (lane < 8) *(bf16x8 *)(sin + hslot) = lh;
+    *(bf16x8 *)(sg + lane * 16) = lg[0];
+    *(bf16x8 *)(sg + 1024 + lane * 16) = lg[1];
+    if (i < a.rows) load(y + 1);
+    __builtin_amdgcn_wave_barrier();
+    const bool in_strip = i + 1 < a.rows;
 #pragma unroll
-      for (int ib = 0; ib < IB; ++ib)
+    for (int cb = 0; cb < 2; ++cb) {
+      gf[0][cb] = gf[1][cb];
+      gf[1][cb] = gf[2][cb];
+      gf[2][cb] = in_strip ? read_tr(sg + word + 32 * cb, 4 * kWgPix) : bf16x8{};
+      acc[36 + cb] = mfma(gf[2][cb], one, acc[36 + cb]);
+    }
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+      for (int ib = 0; ib < 2; ++ib) {
+        const bf16x8 bf = read_tr(sin + word + dx * kWgPix + 32 * ib, 4 * kWgPix);
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+          for (int cb = 0; cb < 2; ++cb) {
+            f32x4 &c = acc[((dy * 3 + dx) * 2 + cb) * 2 + ib];
+            c = mfma(gf[2 - dy][cb], bf, c);
+          }
+      }
+    __builtin_amdgcn_wave_barrier();
+  }
+  if (!u.live)
+#pragma unroll
+    for (int k = 0; k < NT; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+  wg_sum<NT>(acc, &L.sum[0][0][0], wave, lane);
+  if (wave) return;
+  constexpr int P = 9 * kHid * kHid + kHid;
+  float *out = a.partials + (size_t)blockIdx.x * P;
+  // D[m = co][n = ci]: lane n + 16 g, register r -> co = 16 cb + 4 g + r
+  const int n = lane & 15;
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+      for (int ib = 0; ib < 2; ++ib)
+        *(f32x4 *)(out + (t * kHid + 16 * ib + n) * kHid + 16 * cb + 4 * g) =
+            acc[(t * 2 + cb) * 2 + ib];
+  if (n == 0)
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+      *(f32x4 *)(out + 9 * kHid * kHid + 16 * cb + 4 * g) = acc[36 + cb];
+}
+
+// Layers 1 and 3, a 32-channel ("wide") and a 4-channel ("narrow") tensor:
+// sum_p wide[p][w] narrow[p + (dy - 1, dx - 1)][c] for w = 0..31 and the 12 pairs
+// (dx, c), which share one block of 16 columns: 6 products a row.  Layer 1 has the
+// input narrow (kL1: the tap is t = 3 dy + dx), layer 3 the gradient (the tap is
+// 8 - t).  Narrow rows are read one ahead of the wide row; bound by the wide
+// tensor's read.
+template <bool kL1>
+__global__ __launch_bounds__(64 * kWgWaves) __attribute__((amdgpu_waves_per_eu(6)))
+void k_wgrad_hn(WgradArgs a) {
+  constexpr int NT = 8;  // [dy][wide block], 2 bias blocks (layer 3: one)
+  union Shared {
+    char stage[kWgWaves][kWgWide + kWgNarrowHalo + 16];
+    f32x4 sum[2][NT][64];
+  };
+  __shared__ __attribute__((aligned(16))) Shared L;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const WgUnit u = wg_unit(a, wave);
+  const int W = a.W, H = a.H;
+  const long long img = (long long)u.b * H;
+  const bf16 *wide = kL1 ? a.grad : a.in, *narrow = kL1 ? a.in : a.grad;
+  char *const sw = L.stage[wave];
+  char *const sn = L.stage[wave] + kWgWide;  // slot 0: pixel x0 - 1
+  const int g = lane >> 4, e = (lane >> 2) & 3, q = lane & 3;
+  const int wword = (8 * g + e) * kWgPix + 8 * q;
+  // columns 4 dx + c: lane q = dx addresses the pixel dx - 1 further on (q = 3:
+  // columns 12..15, not used)
+  const int nword = (8 * g + e + (q < 3 ? q : 2)) * (2 * kIn);
+  const int nx = wrap(u.x0 - 1 + (lane < 34 ? lane : 33), W);
+
+  bf16x8 lw[2];
+  bf16x4 ln;
+  auto load_wide = [&](const int y) {
+    const char *p = (const char *)(wide + (img + wrap(y, H)) * W * (long long)kHid) +
+                    u.x0 * kWgPix + lane * 16;
+    lw[0] = *(const bf16x8 *)p;
+    lw[1] = *(const bf16x8 *)(p + 1024);
+  };
+  auto load_narrow = [&](const int y) {
+    ln = *(const bf16x4 *)(narrow + ((img + wrap(y, H)) * W + nx) * kIn);
+  };
+  auto narrow_frag = [&]() {
+    if (lane < 34) *(bf16x4 *)(sn + lane * 8) = ln;
+    __builtin_amdgcn_wave_barrier();
+    const bf16x8 f = read_tr(sn + nword, 4 * 2 * kIn);
+    __builtin_amdgcn_wave_barrier();
+    return f;
+  };
+  f32x4 acc[NT];
+#pragma unroll
+  for (int k = 0; k < NT; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const bf16x8 one = ones_frag();
+  bf16x8 nf[3];  // narrow rows y - 1, y, y + 1
+  load_narrow(u.y0 - 1);
+  nf[1] = narrow_frag();
+  load_narrow(u.y0);
+  nf[2] = narrow_frag();
+  load_narrow(u.y0 + 1);
+  load_wide(u.y0);
+  for (int i = 0; i < a.rows; ++i) {
+    const int y = u.y0 + i;
+    *(bf16x8 *)(sw + lane * 16) = lw[0];
+    *(bf16x8 *)(sw + 1024 + lane * 16) = lw[1];
+    nf[0] = nf[1];
+    nf[1] = nf[2];
+    nf[2] = narrow_frag();
+    if (i + 1 < a.rows) {
+      load_wide(y + 1);
+      load_narrow(y + 2);
+    }
+#pragma unroll
+    for (int wb = 0; wb < 2; ++wb) {
+      const bf16x8 wf = read_tr(sw + wword + 32 * wb, 4 * kWgPix);
+#pragma unroll
+      for (int dy = 0; dy < 3; ++dy) acc[2 * dy + wb] = mfma(wf, nf[dy], acc[2 * dy + wb]);
+      if constexpr (kL1) acc[6 + wb] = mfma(wf, one, acc[6 + wb]);
+    }
+    if constexpr (!kL1) acc[6] = mfma(one, nf[1], acc[6]);
+    __builtin_amdgcn_wave_barrier();
+  }
+  if (!u.live)
+#pragma unroll
+    for (int k = 0; k < NT; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+  wg_sum<NT>(acc, &L.sum[0][0][0], wave, lane);
+  if (wave) return;
+  // D[m = wide channel][n = 4 dx + c]: lane n + 16 g, register r -> w = 16 wb + 4 g + r
+  constexpr int P = 9 * kHid * 4 + (kL1 ? kHid : 4);
+  float *out = a.partials + (size_t)blockIdx.x * P;
+  const int n = lane & 15, dx = n >> 2, c = n & 3;
+  if (dx < 3)
+#pragma unroll
+    for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+      for (int wb = 0; wb < 2; ++wb)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const int co = 16 * cb + 4 * g + r, ci = 16 * ib + m;
-          if (co < COUT && ci < CIN) out[((w * 3 + dx) * CIN + ci) * COUT + co] = acc[dx][cb][ib][r];
+          const int w = 16 * wb + 4 * g + r, t = 3 * dy + dx;
+          out[kL1 ? (t * 4 + c) * kHid + w : ((8 - t) * kHid + w) * 4 + c] = acc[2 * dy + wb][r];
         }
-  if (w == 0) {
+  if constexpr (kL1) {
+    if (n == 0)
 #pragma unroll
-    for (int cb = 0; cb < CB; ++cb) {
-      float s = dbacc[cb];
-      s += __shfl_xor(s, 16, 64);
-      s += __shfl_xor(s, 32, 64);
-      const int co = 16 * cb + m;
-      if (g == 0 && co < COUT) out[9 * CIN * COUT + co] = s;
-    }
+      for (int wb = 0; wb < 2; ++wb)
+        *(f32x4 *)(out + 9 * kHid * 4 + 16 * wb + 4 * g) = acc[6 + wb];
+  } else {
+    if (g == 0 && dx == 1) out[9 * kHid * 4 + c] = acc[6][0];
   }
 }
 
-// Sum of the per-workgroup partials into the canonical gradient of one
-// layer, in two fixed-order passes: workgroup column g sums partials g,
-// g + G, g + 2G, ... for 256 parameters, then k_wgrad_final adds the G
-// column sums.
-constexpr int kWgGroups = 32;
+// Sum of the per-workgroup partials of all three layers into the canonical
+// gradient, in a fixed order: wave w of a workgroup adds the partials w, w + 16,
+// ... of 64 parameters, then the waves' sums are added in order.
+constexpr int kWgReduceWaves = 16;
+struct WgReduceArgs {
+  const float *partials[3];
+  int parts[3], size[3], dst[3], first[3];  // first: first workgroup of the layer
+  float *grads;
+};
 
-__global__ __launch_bounds__(256) void k_wgrad_reduce(const float *partials, int nparts, int P,
-                                                       float *colsum) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  const int g = blockIdx.y;
-  if (j >= P) return;
+__global__ __launch_bounds__(64 * kWgReduceWaves) void k_wgrad_reduce(WgReduceArgs a) {
+  __shared__ float sum[kWgReduceWaves][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int l = (int)blockIdx.x >= a.first[2] ? 2 : ((int)blockIdx.x >= a.first[1] ? 1 : 0);
+  const int j = ((int)blockIdx.x - a.first[l]) * 64 + lane, P = a.size[l], n = a.parts[l];
+  const float *p = a.partials[l];
   float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-  int u = g;
-  for (; u + 3 * kWgGroups < nparts; u += 4 * kWgGroups) {
-    s0 += partials[(size_t)u * P + j];
-    s1 += partials[(size_t)(u + kWgGroups) * P + j];
-    s2 += partials[(size_t)(u + 2 * kWgGroups) * P + j];
-    s3 += partials[(size_t)(u + 3 * kWgGroups) * P + j];
+  if (j < P) {
+    int k = w;
+    for (; k + 3 * kWgReduceWaves < n; k += 4 * kWgReduceWaves) {
+      s0 += p[(size_t)k * P + j];
+      s1 += p[(size_t)(k + kWgReduceWaves) * P + j];
+      s2 += p[(size_t)(k + 2 * kWgReduceWaves) * P + j];
+      s3 += p[(size_t)(k + 3 * kWgReduceWaves) * P + j];
+    }
+    for (; k < n; k += kWgReduceWaves) s0 += p[(size_t)k * P + j];
   }
-  for (; u < nparts; u += kWgGroups) s0 += partials[(size_t)u * P + j];
-  colsum[(size_t)g * P + j] = (s0 + s1) + (s2 + s3);
-}
-
-__global__ __launch_bounds__(256) void k_wgrad_final(const float *colsum, int P, float *grad) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= P) return;
-  float s = 0.f;
-#pragma unroll 8
-  for (int g = 0; g < kWgGroups; ++g) s += colsum[(size_t)g * P + j];
-  grad[j] = s;
+  sum[w][lane] = (s0 + s1) + (s2 + s3);
+  __syncthreads();
+  if (w == 0 && j < P) {
+    float s = sum[0][lane];
+#pragma unroll
+    for (int k = 1; k < kWgReduceWaves; ++k) s += sum[k][lane];
+    a.grads[a.dst[l] + j] = s;
+  }
 }
 
 // ---------------------------------------------------------------- loss

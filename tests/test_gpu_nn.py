@@ -140,6 +140,14 @@ def test_gradients_match_oracle(B, H, W):
             gk = C.bf16(gx * (acts[k] > 0))
 
 
+@pytest.mark.parametrize("B,H,W", [(1, 4, 32), (5, 8, 32), (3, 20, 96)])
+def test_gradients_of_ragged_strips_match_oracle(B, H, W):
+    """Weight gradients where the strips of 32 columns are fewest (one wave; the
+    halo columns wrap onto the strip itself), where they do not fill the last
+    workgroup of four waves, and with strips of four rows."""
+    test_gradients_match_oracle(B, H, W)
+
+
 def test_batch_index_selects_samples():
     """idx gathers samples out of a larger pool, for inputs and targets."""
     H, W = 8, 32
