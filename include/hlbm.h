@@ -289,7 +289,9 @@ typedef enum { HLBM_BATCH_STRIPS = 0, HLBM_BATCH_TILES = 1 } hlbm_batch_kernel;
 size_t hlbm_batch_workspace_bytes(const hlbm_params *params, int32_t count);
 
 /* Initialise every domain as hlbm_init does.  params: host array of `count`;
- * rho, ux, uy, s: concatenated device fields.  Synchronises `stream`. */
+ * rho, ux, uy, s: concatenated device fields.  The batch starts on the strip
+ * shape of least modelled time (hlbm_batch_plan reports it; see
+ * hlbm_batch_set_shape and hlbm_batch_autotune).  Synchronises `stream`. */
 int hlbm_batch_init(hlbm_batch **out, const hlbm_params *params, int32_t count, void *workspace,
                     size_t ws_bytes, const void *rho, const void *ux, const void *uy,
                     const void *s, hlbm_stream_t stream);
@@ -326,9 +328,9 @@ int hlbm_batch_set_shape(hlbm_batch *b, int32_t kernel, int32_t tile_w, int32_t 
 int hlbm_batch_set_tile(hlbm_batch *b, int32_t tile_w, int32_t tile_h, hlbm_stream_t stream);
 
 /* Time `steps` steps (after one untimed launch; rounded up to even when the
- * strip kernel takes two steps per launch) for every shape that
- * hlbm_batch_set_shape accepts among strips {64, 120, 128, 184, 192, 256} x {4, 8, 16,
- * 32, 64, 128} and all tile shapes, twice each, keep the fastest and report
+ * strip kernel takes two steps per launch) for the fourteen strip shapes of
+ * least modelled time (widths hlbm_batch_set_shape accepts, 4 to 128 rows) and
+ * all tile shapes, twice each, keep the fastest and report
  * its kernel and shape (outputs may be NULL).  scratch: a device buffer of hlbm_batch_state_bytes(b) bytes
  * owned by the caller; the state at entry is saved there and loaded again
  * (divergence flags cleared) before every trial, so all shapes time the same

@@ -547,7 +547,6 @@ struct hlbm_batch {
              every == o.every && pending == o.pending && net == o.net;
     }
   } cgraph_key[2];
-  int xcd_walk = 0;  // batch kernels: each XCD walks a contiguous range of the items
 };
 
 namespace {
@@ -555,14 +554,11 @@ namespace {
 // strip widths; 120 and 184 (tile plus halo in two and three whole waves)
 // for two-step strips only, FP32
 constexpr int kBatchTileW[6] = {64, 120, 128, 184, 192, 256};
+// strip heights the autotuner ranks, and how many strip shapes it times
+constexpr int kTuneRows[] = {4,  5,  6,  7,  8,  9,  10, 12, 14, 16, 18,  20,
+                             24, 28, 32, 40, 48, 56, 64, 80, 96, 112, 128};
+constexpr size_t kTuneStrips = 14;
 constexpr int kBatchMinRows = 4;  // short strips: small domains are bound by the serial sweep
-// Batches whose two state buffers fit in this many bytes (the 256 MiB
-// last-level cache) walk their items XCD by XCD, which keeps neighbouring
-// tiles' halos in one L2: 8 x 256^2 two-step tiles 14.3 -> 13.2 us per step,
-// one-step 32 x 16 tiles 18.8 -> 15.0, 8 x 128^2 7.6 -> 5.8.  Larger batches
-// stream from HBM, where the round-robin walk measured faster (8 x 1024^2
-// strips 117.5 against 133 us per step).
-constexpr size_t kXcdWalkBytes = (size_t)256 << 20;
 // shapes of the two-dimensional tile kernel, tried in this order by the autotuner
 constexpr int kTileShapes[5][2] = {{32, 8}, {32, 16}, {64, 8}, {32, 32}, {64, 16}};
 
@@ -608,7 +604,6 @@ void batch_layout(hlbm_batch *b) {
   }
   b->nodes = facc;
   b->state_bytes = round_up((size_t)acc * el, kAlign);
-  b->xcd_walk = 2 * b->state_bytes <= kXcdWalkBytes ? 1 : 0;
   // the most items any shape gives: the narrowest strips or the smallest tiles
   b->max_items = std::max(batch_items_for(b, 64, kBatchMinRows, nullptr),
                           batch_items_for(b, 32, 8, nullptr));
@@ -645,6 +640,58 @@ bool batch_shape_ok(const hlbm_batch *b, int kind, int tw, int th) {
   if (b->spl_strips == 2 && (tw == 256 || (b->dtype == HLBM_F64 && tw == 192)))
     return false;  // the two-step strip kernel's widths
   return th >= kBatchMinRows;
+}
+
+// Resident workgroups per compute unit of the strip kernel of width tw.
+int batch_resident(const hlbm_batch *b, int tw) {
+  if (b->spl_strips == 2)
+    return b->dtype == HLBM_F64 ? hlbm::f64::batch2_blocks_per_cu(tw)
+                                : hlbm::f32::batch2_blocks_per_cu(tw);
+  return b->dtype == HLBM_F64 ? hlbm::f64::batch_blocks_per_cu(tw)
+                              : hlbm::f32::batch_blocks_per_cu(tw);
+}
+
+// Strip shapes by modelled time (see sweep_cost), at most four heights of a width.
+struct BatchShape {
+  int kind, w, h;
+  long long cost;
+};
+std::vector<BatchShape> ranked_strips(const hlbm_batch *b) {
+  auto cheaper = [](const BatchShape &x, const BatchShape &y) { return x.cost < y.cost; };
+  std::vector<BatchShape> all;
+  for (int tw : kBatchTileW) {
+    const int per_cu = batch_resident(b, tw);
+    const int waves = b->spl_strips == 2 ? (tw + 8 + 63) / 64 : (tw + 64) / 64;
+    std::vector<BatchShape> of_width;
+    for (int th : kTuneRows) {
+      if (!batch_shape_ok(b, HLBM_BATCH_STRIPS, tw, th)) continue;
+      long long nb = 0;
+      for (const hlbm_params &p : b->params) {
+        const int rows = std::min(th, (int)p.ny);
+        nb += (long long)((p.nx + tw - 1) / tw) * ((p.ny + rows - 1) / rows);
+      }
+      const int es = (int)elem_size(b->dtype);
+      of_width.push_back({HLBM_BATCH_STRIPS, tw, th,
+                          hlbm::sweep_cost(nb, th, waves, per_cu, b->spl_strips, es)});
+    }
+    std::stable_sort(of_width.begin(), of_width.end(), cheaper);
+    of_width.resize(std::min<size_t>(of_width.size(), 4));
+    all.insert(all.end(), of_width.begin(), of_width.end());
+  }
+  std::stable_sort(all.begin(), all.end(), cheaper);
+  return all;
+}
+
+// Shape a batch starts with: the strips of least modelled time; of at most 64
+// rows where the state is larger than the last-level cache (taller strips spread
+// the resident rows over it; 8192^2: 64 rows 631 us per step, 96 697).  A fixed
+// 128 x 32 took 670 us for two steps of 16 x 1024^2 domains, the modelled shape
+// 375.
+BatchShape initial_strips(const hlbm_batch *b) {
+  const bool large = 2 * b->state_bytes > ((size_t)256 << 20);
+  for (const BatchShape &s : ranked_strips(b))
+    if (!large || s.h <= 64) return s;
+  return BatchShape{HLBM_BATCH_STRIPS, 128, 32, 0};
 }
 
 // Item list and grids of shape (kind, tw, th); the shape must be one
@@ -755,33 +802,33 @@ hipError_t batch_launch_spl(hlbm_batch *b, int from, int spl, hipStream_t st,
   if (b->kind == HLBM_BATCH_TILES && spl == 2) {
     if (b->dtype == HLBM_F64)
       return hlbm::f64::step_tile_batch2(doms, offs, items, b->nitems, src, dst, stat,
-                                         b->tile_w, b->tile_h, b->grid, b->xcd_walk, mom, foffs,
+                                         b->tile_w, b->tile_h, b->grid, mom, foffs,
                                          b->nodes, cr, st);
     return hlbm::f32::step_tile_batch2(doms, offs, items, b->nitems, src, dst, stat, b->tile_w,
-                                       b->tile_h, b->grid, b->xcd_walk, mom, foffs, b->nodes, cr,
+                                       b->tile_h, b->grid, mom, foffs, b->nodes, cr,
                                        st);
   }
   if (b->kind == HLBM_BATCH_TILES) {
     if (b->dtype == HLBM_F64)
       return hlbm::f64::step_tile_batch(doms, offs, items, b->nitems, src, dst, stat, b->tile_w,
-                                        b->tile_h, b->grid1, b->xcd_walk, mom, foffs, b->nodes,
+                                        b->tile_h, b->grid1, mom, foffs, b->nodes,
                                         cr, st);
     return hlbm::f32::step_tile_batch(doms, offs, items, b->nitems, src, dst, stat, b->tile_w,
-                                      b->tile_h, b->grid1, b->xcd_walk, mom, foffs, b->nodes, cr,
+                                      b->tile_h, b->grid1, mom, foffs, b->nodes, cr,
                                       st);
   }
   if (spl == 2) {
     if (b->dtype == HLBM_F64)
       return hlbm::f64::step_batch2(doms, offs, items, b->nitems, src, dst, stat, b->tile_h,
-                                    b->tile_w, b->grid, b->xcd_walk, st);
+                                    b->tile_w, b->grid, st);
     return hlbm::f32::step_batch2(doms, offs, items, b->nitems, src, dst, stat, b->tile_h,
-                                  b->tile_w, b->grid, b->xcd_walk, st);
+                                  b->tile_w, b->grid, st);
   }
   if (b->dtype == HLBM_F64)
     return hlbm::f64::step_batch(doms, offs, items, b->nitems, src, dst, stat, b->tile_h,
-                                 b->tile_w, b->grid1, b->xcd_walk, st);
+                                 b->tile_w, b->grid1, st);
   return hlbm::f32::step_batch(doms, offs, items, b->nitems, src, dst, stat, b->tile_h,
-                               b->tile_w, b->grid1, b->xcd_walk, st);
+                               b->tile_w, b->grid1, st);
 }
 
 // One launch of the batch's kernel (b->spl steps) from buffer `from`.
@@ -890,7 +937,10 @@ int hlbm_batch_init(hlbm_batch **out, const hlbm_params *params, int32_t count, 
     e = b->dtype == HLBM_F64 ? hlbm::f64::init(b->doms[k], r, u, v, sv, dst, st)
                              : hlbm::f32::init(b->doms[k], r, u, v, sv, dst, st);
   }
-  if (e == hipSuccess) e = batch_upload_items(b, HLBM_BATCH_STRIPS, 128, 32, st);  // synchronises
+  if (e == hipSuccess) {
+    const BatchShape s0 = initial_strips(b);
+    e = batch_upload_items(b, s0.kind, s0.w, s0.h, st);  // synchronises
+  }
   if (e != hipSuccess) {
     delete b;
     return HLBM_EHIP;
@@ -971,21 +1021,16 @@ int hlbm_batch_autotune(hlbm_batch *b, int32_t steps, void *scratch, int32_t *ho
                         int32_t *host_best_w, int32_t *host_best_h, hlbm_stream_t stream) {
   if (!b || steps < 1 || !scratch) return HLBM_EINVAL;
   hipStream_t st = (hipStream_t)stream;
-  // candidate shapes: strips {64, 120, 128, 184, 192, 256} x {4, ..., 128}, then tiles
-  struct Shape {
-    int kind, w, h;
-  };
-  std::vector<Shape> cand;
-  for (int tw : kBatchTileW)
-    for (int th : {4, 8, 16, 32, 64, 128})
-      if (batch_shape_ok(b, HLBM_BATCH_STRIPS, tw, th)) cand.push_back({HLBM_BATCH_STRIPS, tw, th});
+  // candidates: the strips of least modelled time, then the tiles
+  std::vector<BatchShape> cand = ranked_strips(b);
+  cand.resize(std::min<size_t>(cand.size(), kTuneStrips));
   for (const auto &t : kTileShapes)
     if (batch_shape_ok(b, HLBM_BATCH_TILES, t[0], t[1]))
-      cand.push_back({HLBM_BATCH_TILES, t[0], t[1]});
+      cand.push_back({HLBM_BATCH_TILES, t[0], t[1], 0});
   if (b->spl_strips == 2 && steps % 2) ++steps;  // whole launches of either kernel
-  constexpr int kRepeats = 2;  // best of two timings per shape
+  constexpr int kRepeats = 2;  // best of two timings per shape, apart in time (clocks drift)
   float best = 1e30f;
-  Shape bs{b->kind, b->tile_w, b->tile_h};
+  BatchShape bs{b->kind, b->tile_w, b->tile_h, 0};
   const int64_t steps0 = b->steps;
   hipEvent_t e0, e1;
   if (hipEventCreate(&e0) != hipSuccess) return HLBM_EHIP;
@@ -996,8 +1041,8 @@ int hlbm_batch_autotune(hlbm_batch *b, int32_t steps, void *scratch, int32_t *ho
   // every trial starts from the state at entry, with the divergence flags
   // cleared, so each shape times the same work; the state is restored at the end
   int rc = hlbm_batch_save_state(b, scratch, stream);
-  for (const Shape &c : cand) {
-    for (int rep = 0; rep < kRepeats && rc == HLBM_OK; ++rep) {
+  for (int rep = 0; rep < kRepeats && rc == HLBM_OK; ++rep) {
+    for (const BatchShape &c : cand) {
       if (hlbm_batch_load_state(b, scratch, stream) != HLBM_OK) { rc = HLBM_EHIP; break; }
       if (batch_upload_items(b, c.kind, c.w, c.h, st) != hipSuccess) { rc = HLBM_EHIP; break; }
       if (hlbm_batch_step(b, b->spl, 0, st) != HLBM_OK) { rc = HLBM_EHIP; break; }
@@ -1012,7 +1057,6 @@ int hlbm_batch_autotune(hlbm_batch *b, int32_t steps, void *scratch, int32_t *ho
         bs = c;
       }
     }
-    if (rc != HLBM_OK) break;
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);

@@ -908,22 +908,22 @@ struct BatchArgs {
   const float *cx, *cdl;
   const double *cparts;
   int cconserve;
-  int xcd_walk;  // 1: each XCD walks a contiguous range of the items (see tile_walk)
 };
 
 // This workgroup's share of the persistent walk over n items: items first,
 // first + step, ... below end.  Workgroups are dealt round-robin to the
-// eight XCDs (workgroup b to XCD b mod 8).  With xcd set (and at least eight
-// workgroups) the walk gives XCD x the contiguous item range
-// [x n / 8, (x + 1) n / 8), taken in order by its workgroups, so tiles and
-// strips that share halo rows and columns are loaded through one L2;
-// otherwise workgroup b takes every gridDim.x-th item from b.
+// eight XCDs (workgroup b to XCD b mod 8); with at least eight workgroups XCD x
+// gets the contiguous item range [x n / 8, (x + 1) n / 8), taken in order by its
+// workgroups, so tiles and strips that share halo rows and columns, and the cache
+// lines their rows share, go through one L2: 8 x 256^2 two-step tiles 14.3 -> 13.2
+// us per step, 8 x 128^2 7.6 -> 5.8; also batches larger than the last-level cache
+// (16 x 1024^2 strips 189 -> 181, 48 mixed domains 81.8 -> 80.5).
 struct TileWalk {
   int first, step, end;
 };
-__device__ __forceinline__ TileWalk tile_walk(const int n, const int xcd) {
+__device__ __forceinline__ TileWalk tile_walk(const int n) {
   const int g = (int)gridDim.x, b = (int)blockIdx.x;
-  if (!xcd || g < 8) return TileWalk{b, g, n};
+  if (g < 8) return TileWalk{b, g, n};
   const int x = b & 7;
   const int lo = (int)((long long)x * n / 8), hi = (int)((long long)(x + 1) * n / 8);
   return TileWalk{lo + (b >> 3), (g - x + 7) >> 3, hi};
@@ -933,7 +933,7 @@ template <int CW>
 __global__ __launch_bounds__(CW + 64) __attribute__((amdgpu_waves_per_eu(HLBM_IS_F32 ? 4 : 3)))
 void k_step_batch(BatchArgs a) {
   __shared__ LevelRings<CW + 4> R;
-  const TileWalk walk = tile_walk(a.nitems, a.xcd_walk);
+  const TileWalk walk = tile_walk(a.nitems);
   for (int it = walk.first; it < walk.end; it += walk.step) {
     const int4 w = a.items[it];
     const int dm = __builtin_amdgcn_readfirstlane(w.x);

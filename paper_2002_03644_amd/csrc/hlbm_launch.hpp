@@ -103,20 +103,41 @@ inline TileShape step2_tile(int nx, int ny, int tile_w, int tile_h, int elem_siz
   return t;
 }
 
+// Modelled time of a row sweep over nb tiles of `rows` rows, `per_cu` workgroups
+// of `waves` waves resident per compute unit: full rounds at the resident load
+// plus the rest at its own, each (rows + fill of the pipeline) iterations of the
+// time an iteration takes with that many waves per SIMD (measured on grids in the
+// last-level cache, in units of 10 ns, by half waves per SIMD from one half up;
+// below about two waves it hardly rises, the sweep then waits on its own
+// latencies).
+constexpr int kModelCUs = 256;
+inline long long sweep_cost(long long nb, int rows, int waves, int per_cu, int steps,
+                            int elem_size) {
+  static const int t_two[] = {145, 173, 178, 186, 232, 240};
+  static const int t_one32[] = {115, 124, 140, 160, 182, 205, 225, 240, 260, 280, 305, 330};
+  static const int t_one64[] = {185, 190, 257, 285, 330, 400};
+  const int *time = steps == 2 ? t_two : (elem_size == 4 ? t_one32 : t_one64);
+  const int last = steps == 2 ? 5 : (elem_size == 4 ? 11 : 5), fill = steps == 2 ? 8 : 4;
+  auto iter = [&](int wgs_per_cu) {  // ceil(2 wgs waves / 4), as an index
+    const int k = (wgs_per_cu * waves + 1) / 2 - 1;
+    return time[k > last ? last : k];
+  };
+  const int resident = kModelCUs * per_cu;
+  const long long rounds = nb < (1 << 30) ? (int)nb / resident : nb / resident;
+  const int rest = (int)(nb - rounds * resident);
+  return (rows + fill) *
+         (rounds * iter(per_cu) + (rest ? iter((rest + kModelCUs - 1) / kModelCUs) : 0));
+}
+
 // Tile shape that an automatic launch takes (tile_w and tile_h both left to
 // the library) in place of the nominal one above, on grids of a few rounds of
-// resident workgroups.  There the time is a whole number of rounds times the
-// sweep's iterations (output rows plus the fill of its pipeline), so a strip
-// height from a fixed list can leave the last round nearly empty: 1500 x 1100
-// in two-step strips of 184 x 8 is 1242 workgroups, a second round of 218.  The
-// shape is the one of least modelled time over all widths and heights: full
-// rounds at the resident load plus the rest at its own, each (rows + fill)
-// iterations of the time an iteration takes with that many waves per SIMD
-// (measured, in units of 10 ns; below about two waves it hardly rises, the
-// sweep then waits on its own latencies).  us per step, nominal -> fitted:
-// FP32 two-step 1500 x 1100 31.0 -> 21.7, 900^2 (one step before) 23.2 -> 15.1,
-// 500^2 11.8 -> 9.7, 200^2 9.9 -> 7.1, 2048^2 55.2 -> 50.4; one-step 2048 x 512
-// 26.8 -> 23.9; FP64 600^2 25.8 -> 23.7, 200^2 13.9 -> 11.4.
+// resident workgroups.  There a strip height from a fixed list can leave the last
+// round nearly empty: 1500 x 1100 in two-step strips of 184 x 8 is 1242
+// workgroups, a second round of 218.  The shape is the one of least modelled time
+// over all widths and heights.  us per step, nominal -> fitted: FP32 two-step
+// 1500 x 1100 31.0 -> 21.7, 900^2 (one step before) 23.2 -> 15.1, 500^2 11.8 ->
+// 9.7, 200^2 9.9 -> 7.1, 2048^2 55.2 -> 50.4; one-step 2048 x 512 26.8 -> 23.9;
+// FP64 600^2 25.8 -> 23.7, 200^2 13.9 -> 11.4.
 //
 // Grids of at least four full rounds of nominal tiles keep those: their rounds
 // even out and memory bounds them (8192^2: 64 rows 631 us per step, 48 644,
@@ -125,42 +146,27 @@ struct FitShape {
   int bw, waves, per_cu, max_nx;  // width, waves per workgroup, resident workgroups per CU
 };
 inline TileShape fit_tile(int nx, int ny, const TileShape &nominal, int elem_size, int steps) {
-  constexpr long long kCUs = 256;
   static const FitShape two[] = {{64, 2, 6, 64}, {120, 2, 6, 1 << 30}, {184, 3, 4, 1 << 30}};
   static const FitShape one32[] = {
       {64, 2, 12, 1 << 30}, {128, 3, 8, 1 << 30}, {192, 4, 6, 1 << 30}, {256, 5, 4, 1 << 30}};
   static const FitShape one64[] = {{64, 2, 6, 1 << 30}, {128, 3, 4, 1 << 30}, {192, 4, 3, 1 << 30}};
-  // time of an iteration by half waves per SIMD, from one half up
-  static const int t_two[] = {145, 173, 178, 186, 232, 240};
-  static const int t_one32[] = {115, 124, 140, 160, 182, 205, 225, 240, 260, 280, 305, 330};
-  static const int t_one64[] = {185, 190, 257, 285, 330, 400};
   const FitShape *shapes = steps == 2 ? two : (elem_size == 4 ? one32 : one64);
   const int count = steps == 2 ? 3 : (elem_size == 4 ? 4 : 3);
-  const int *time = steps == 2 ? t_two : (elem_size == 4 ? t_one32 : t_one64);
-  const int fill = steps == 2 ? 8 : 4;
   auto tiles = [&](int bw, int rows) {
     return (long long)((nx + bw - 1) / bw) * ((ny + rows - 1) / rows);
   };
   for (int k = 0; k < count; ++k)
     if (shapes[k].bw == nominal.bw &&
-        tiles(nominal.bw, nominal.rows) >= 4 * kCUs * shapes[k].per_cu)
+        tiles(nominal.bw, nominal.rows) >= 4LL * kModelCUs * shapes[k].per_cu)
       return nominal;
   TileShape best = nominal;
   long long least = -1;
   for (int k = 0; k < count; ++k) {
     const FitShape &f = shapes[k];
     if (nx > f.max_nx) continue;
-    const int nbx = (nx + f.bw - 1) / f.bw, resident = (int)kCUs * f.per_cu;
-    auto iter = [&](int wgs_per_cu) {  // ceil(2 wgs waves / 4), as an index
-      return time[(wgs_per_cu * f.waves + 1) / 2 - 1];
-    };
     for (int rows = ny < 2 ? ny : 2; rows <= ny && rows <= 128; rows += rows < 48 ? 1 : 4) {
-      const long long all = (long long)nbx * ((ny + rows - 1) / rows);
-      if (all > (1 << 24)) continue;
-      const int nb = (int)all, rounds = nb / resident, rest = nb - rounds * resident;
       const long long cost =
-          (long long)(rows + fill) * (rounds * iter(f.per_cu) +
-                                      (rest ? iter((rest + (int)kCUs - 1) / (int)kCUs) : 0));
+          sweep_cost(tiles(f.bw, rows), rows, f.waves, f.per_cu, steps, elem_size);
       if (least < 0 || cost < least) {
         least = cost;
         best.bw = f.bw;
@@ -227,22 +233,22 @@ struct TileCorr {
   void pack_domains(const HostDomain *h, int count, void *host_out);                        \
   hipError_t step_batch(const void *doms, const long long *offs, const void *items,          \
                         int nitems, const void *src, void *dst, unsigned *status, int rows, \
-                        int cw, int grid, int xcd_walk, hipStream_t st);                    \
+                        int cw, int grid, hipStream_t st);                    \
   int batch_blocks_per_cu(int cw);                                                          \
   hipError_t step_batch2(const void *doms, const long long *offs, const void *items,         \
                          int nitems, const void *src, void *dst, unsigned *status, int rows,\
-                         int cw, int grid, int xcd_walk, hipStream_t st);                   \
+                         int cw, int grid, hipStream_t st);                   \
   int batch2_blocks_per_cu(int cw);                                                         \
   hipError_t step_tile_batch(const void *doms, const long long *offs, const void *items,     \
                              int nitems, const void *src, void *dst, unsigned *status,       \
-                             int tw, int th, int grid, int xcd_walk, void *mom,              \
+                             int tw, int th, int grid, void *mom,              \
                              const long long *foffs,                                         \
                              long long mom_sc, const TileCorr &corr, hipStream_t st);        \
   int tile_blocks_per_cu(int tw, int th);                                                   \
   bool tile_shape_supported(int tw, int th);                                                \
   hipError_t step_tile_batch2(const void *doms, const long long *offs, const void *items,    \
                               int nitems, const void *src, void *dst, unsigned *status,      \
-                              int tw, int th, int grid, int xcd_walk, void *mom,             \
+                              int tw, int th, int grid, void *mom,             \
                               const long long *foffs,                                        \
                               long long mom_sc, const TileCorr &corr, hipStream_t st);       \
   int tile2_blocks_per_cu(int tw, int th);                                                  \

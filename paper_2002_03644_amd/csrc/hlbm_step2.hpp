@@ -192,7 +192,7 @@ template <int CW>
 __global__ __launch_bounds__(step2_threads(CW))
 __attribute__((amdgpu_waves_per_eu(HLBM_IS_F32 ? 3 : 1))) void k_step_batch2(BatchArgs a) {
   __shared__ TileRings2<CW> R;
-  const TileWalk walk = tile_walk(a.nitems, a.xcd_walk);
+  const TileWalk walk = tile_walk(a.nitems);
   for (int it = walk.first; it < walk.end; it += walk.step) {
     const int4 w = a.items[it];
     const int dm = __builtin_amdgcn_readfirstlane(w.x);
