@@ -149,8 +149,9 @@ int hlbm_validate(const hlbm_params *p);
  * with tile_w and tile_h both 0, hlbm_step fits width and height to whole
  * rounds of the device's resident workgroups on grids of fewer than four such
  * rounds, and there also takes FP32 domains periodic along both axes two steps
- * at a time below 900,000 nodes unless steps_per_launch is 1 (results are the
- * same bit for bit).  Host-only; callable without a GPU. */
+ * at a time below 900,000 nodes unless steps_per_launch is 1, and domains of at
+ * most 1024 nodes (counting a ghost ring on clamped axes) all at once in one
+ * workgroup unless steps_per_launch is given (results are the same bit for bit).  Host-only; callable without a GPU. */
 int hlbm_launch_shape(const hlbm_params *p, int32_t *host_tile_w, int32_t *host_tile_h);
 
 /* Launch plan of hlbm_step for these parameters: steps per kernel launch (1

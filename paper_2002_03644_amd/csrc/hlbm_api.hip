@@ -60,6 +60,7 @@ struct hlbm_handle {
   hlbm::TileShape tile;   // one step per launch
   hlbm::TileShape tile2;  // two steps per launch
   int spl;                // steps per launch (1 or 2)
+  bool resident;          // all steps of a call in one workgroup (tiny domains)
   Layout L;
   char *ws;
   int cur;
@@ -181,7 +182,10 @@ void plan_launches(hlbm_handle *h) {
   h->tile = default_tile(p);
   h->tile2 = default_tile2(p);
   h->spl = steps_per_launch(p);
+  h->resident = false;
   if (p->tile_w || p->tile_h) return;
+  h->resident = !p->steps_per_launch &&
+                hlbm::resident_nodes(p->nx, p->ny, p->bc_x, p->bc_y) <= hlbm::kResidentNodes;
   h->spl = batch_steps_per_launch(p);
   if (h->spl == 2) {  // (its odd last step keeps the nominal one-step shape)
     if (es == 4) h->tile2 = hlbm::fit_tile(p->nx, p->ny, h->tile2, es, 2);
@@ -329,6 +333,17 @@ int hlbm_step(hlbm_handle *h, int32_t nsteps, hlbm_stream_t stream) {
   if (!h || nsteps < 0) return HLBM_EINVAL;
   hipStream_t st = (hipStream_t)stream;
   int32_t n = 0;
+  while (h->resident && n < nsteps) {
+    const int32_t k = std::min(nsteps - n, hlbm::kResidentSteps);
+    const hipError_t e =
+        h->p.dtype == HLBM_F64
+            ? hlbm::f64::resident(h->dom, buf(h, h->cur), buf(h, h->cur ^ 1), status_word(h), k, st)
+            : hlbm::f32::resident(h->dom, buf(h, h->cur), buf(h, h->cur ^ 1), status_word(h), k, st);
+    if (e != hipSuccess) return HLBM_EHIP;
+    h->cur ^= 1;
+    h->steps += k;
+    n += k;
+  }
   if (h->spl == 2) {  // periodic domains, no walls
     for (; n + 2 <= nsteps; n += 2) {
       hipError_t e =

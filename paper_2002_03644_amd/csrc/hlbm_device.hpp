@@ -1058,34 +1058,19 @@ struct WallArgs {
   real *state;  // plane 0 of the current state
 };
 
-__device__ __forceinline__ void wall_node(const WallArgs &a, const int t) {
-  const DomainArgs &d = a.d;
-  const int side = t >= d.nx ? 1 : 0;
-  const int x = t - side * d.nx;
-  const int yw = side ? d.ny - 1 : 0, dir = side ? -1 : 1;
+// One wall node from its streamed populations F[0..8] and the new velocities of the
+// next two rows inside; its populations and entropy in place.  side: 0 the wall
+// y = 0, 1 the other.
+__device__ __forceinline__ void wall_rebuild(const DomainArgs &d, const int side, real (&F)[kPlanes],
+                                             const real u1x, const real u1y, const real u2x,
+                                             const real u2y) {
+  const int dir = side ? -1 : 1;
   const real U = side ? d.wall_u_hi : d.wall_u_lo;
-  const long long P = d.plane;
-  real *node = a.state + (long long)yw * d.pitch + x;
-  real F[kQ];
-#pragma unroll
-  for (int q = 0; q < kQ; ++q) F[q] = node[q * P];
   // arrived from the interior: c_y = -1 (4, 7, 8) at y = 0, c_y = +1 (2, 5, 6) at the top;
   // the rest state's share of the sum is exactly rho_ref, so this is rho_w - rho_ref
   const real in = side ? (F[2] + F[5]) + F[6] : (F[4] + F[7]) + F[8];
   const real dr = ((F[0] + F[1]) + F[3]) + real(2) * in;
   const real rho = dr + d.rho_ref;
-  auto velocity = [&](int y, real &ux, real &uy) {
-    const real *p = a.state + (long long)y * d.pitch + x;
-    real G[kQ];
-#pragma unroll
-    for (int q = 0; q < kQ; ++q) G[q] = p[q * P];
-    const NodeMoments m = node_moments(G, d);
-    ux = m.jx / m.rho;
-    uy = m.jy / m.rho;
-  };
-  real u1x, u1y, u2x, u2y;
-  velocity(yw + dir, u1x, u1y);
-  velocity(yw + 2 * dir, u2x, u2y);
   const real half = real(0.5) * real(dir);
   const real dyux = half * ((real(4) * u1x - u2x) - real(3) * U);
   const real dyuy = half * (real(4) * u1y - u2y);
@@ -1117,9 +1102,36 @@ __device__ __forceinline__ void wall_node(const WallArgs &a, const int t) {
   real f[kQ];
   project(dr, rho * U, real(0), Axx, Axy, Ayy, Axxy, Axyy, Axxyy, f);
 #pragma unroll
-  for (int q = 0; q < kQ; ++q) node[q * P] = f[q];
+  for (int q = 0; q < kQ; ++q) F[q] = f[q];
   // s_w - s_ref = c_v (ln(theta_w / theta_ref) - (gamma - 1) ln(rho_w / rho_ref))
-  node[9 * P] = (log_r(th) - log_r(d.theta_ref) - d.gm1 * (log_r(rho) - d.log_rho_ref)) / d.inv_cv;
+  F[9] = (log_r(th) - log_r(d.theta_ref) - d.gm1 * (log_r(rho) - d.log_rho_ref)) / d.inv_cv;
+}
+
+__device__ __forceinline__ void wall_node(const WallArgs &a, const int t) {
+  const DomainArgs &d = a.d;
+  const int side = t >= d.nx ? 1 : 0;
+  const int x = t - side * d.nx;
+  const int yw = side ? d.ny - 1 : 0, dir = side ? -1 : 1;
+  const long long P = d.plane;
+  real *node = a.state + (long long)yw * d.pitch + x;
+  real F[kPlanes];
+#pragma unroll
+  for (int q = 0; q < kQ; ++q) F[q] = node[q * P];
+  auto velocity = [&](int y, real &ux, real &uy) {
+    const real *p = a.state + (long long)y * d.pitch + x;
+    real G[kQ];
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) G[q] = p[q * P];
+    const NodeMoments m = node_moments(G, d);
+    ux = m.jx / m.rho;
+    uy = m.jy / m.rho;
+  };
+  real u1x, u1y, u2x, u2y;
+  velocity(yw + dir, u1x, u1y);
+  velocity(yw + 2 * dir, u2x, u2y);
+  wall_rebuild(d, side, F, u1x, u1y, u2x, u2y);
+#pragma unroll
+  for (int q = 0; q < kPlanes; ++q) node[q * P] = F[q];
 }
 
 __global__ void k_wall(WallArgs a) {
@@ -1127,6 +1139,14 @@ __global__ void k_wall(WallArgs a) {
   for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x)
     wall_node(a, t);
 }
+
+}  // namespace HLBM_NS
+}  // namespace hlbm
+
+#include "hlbm_resident.hpp"
+
+namespace hlbm {
+namespace HLBM_NS {
 
 // ------------------------------------------------------------ moments
 struct FieldArgs {

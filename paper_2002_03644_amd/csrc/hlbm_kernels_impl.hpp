@@ -121,6 +121,24 @@ hipError_t step2(const HostDomain &h, const void *src, void *dst, unsigned *stat
   return hipGetLastError();
 }
 
+hipError_t resident(const HostDomain &h, const void *src, void *dst, unsigned *status, int steps,
+                    hipStream_t st) {
+  const int next = resident_nodes(h.nx, h.ny, h.bcx, h.bcy);
+  if (next > kResidentNodes) return hipErrorInvalidValue;
+  ResidentArgs a;
+  a.d = to_device(h);
+  a.src = (const real *)src;
+  a.dst = (real *)dst;
+  a.status = status;
+  a.steps = steps;
+  a.next = next;
+  if (next <= kResidentThreads)
+    hipLaunchKernelGGL(k_resident<1>, dim3(1), dim3(kResidentThreads), 0, st, a);
+  else
+    hipLaunchKernelGGL(k_resident<2>, dim3(1), dim3(kResidentThreads), 0, st, a);
+  return hipGetLastError();
+}
+
 hipError_t wall(const HostDomain &h, void *state, hipStream_t st) {
   WallArgs a;
   a.d = to_device(h);

@@ -177,6 +177,17 @@ inline TileShape fit_tile(int nx, int ny, const TileShape &nominal, int elem_siz
   return best;
 }
 
+// Domains of at most this many nodes, counting the ghosts at distance one on
+// clamped axes, are stepped by one workgroup that holds them (k_resident): two
+// nodes a thread fill its LDS in FP64.
+constexpr int kResidentNodes = 1024;
+inline int resident_nodes(long long nx, long long ny, int bcx, int bcy) {
+  const long long n = (nx + (bcx ? 2 : 0)) * (ny + (bcy ? 2 : 0));
+  return n > kResidentNodes ? kResidentNodes + 1 : (int)n;
+}
+// Steps of one such launch at most (about 10 ms).
+constexpr int kResidentSteps = 4096;
+
 // Elements from one state row to the next: nx rounded up to 64, so that every
 // row, and with it every tile's row segment, starts 256-byte aligned (FP32).
 // Rows of other widths lost 5 % (6000 and 14000 columns, rows 64-byte
@@ -218,6 +229,8 @@ struct TileCorr {
                   const TileShape &tile, hipStream_t st);                                   \
   hipError_t step2(const HostDomain &d, const void *src, void *dst, unsigned *status,       \
                    const TileShape &tile, hipStream_t st);                                  \
+  hipError_t resident(const HostDomain &d, const void *src, void *dst, unsigned *status,    \
+                      int steps, hipStream_t st);                                          \
   hipError_t init(const HostDomain &d, const void *rho, const void *ux, const void *uy,     \
                   const void *s, void *dst, hipStream_t st);                                \
   hipError_t wall(const HostDomain &d, void *state, hipStream_t st);                        \

@@ -143,3 +143,26 @@ def test_fitted_launches_equal_given_tiles(nx, ny, opts, dt):
     auto = run(Params(nx, ny, **base), f, 5)
     given = run(Params(nx, ny, tile_w=128, tile_h=8, steps_per_launch=1, **base), f, 5)
     assert torch.equal(state(auto), state(given))
+
+
+@pytest.mark.parametrize("nx,ny,opts", [
+    (1, 1, {}), (3, 2, {}), (32, 32, {}), (512, 1, {}), (19, 27, {}),
+    (30, 30, dict(bc_x="extrapolate", bc_y="extrapolate")),        # 1024 with the ghosts
+    (1, 9, dict(bc_x="extrapolate")), (40, 20, dict(bc_y="extrapolate", phi_mode="fd")),
+    (7, 4, dict(bc_x="extrapolate", bc_y="wall", wall_theta=0.2, wall_ux_hi=0.05)),
+    (10, 100, dict(bc_y="wall", wall_theta=0.2, wall_ux_lo=-0.02, precise_theta=True)),
+])
+@pytest.mark.parametrize("dt", ["f32", "f64"])
+def test_resident_domain_equals_sweeps(nx, ny, opts, dt):
+    """Domains held by one workgroup (up to 1024 nodes with the ghosts of clamped
+    axes, one and two nodes a thread) against the row sweep with a given tile, bit
+    for bit, over two calls."""
+    f = hi.random_smooth(nx, ny, seed=nx + 3 * ny, amp=0.03, u0=(0.12, -0.08))
+    base = dict(dtype=dt, mu=2e-3, sigma=0.3, **opts)
+    auto, given = run(Params(nx, ny, **base), f, 5), run(
+        Params(nx, ny, tile_w=64, tile_h=8, steps_per_launch=1, **base), f, 5)
+    assert torch.equal(state(auto), state(given))
+    auto.step(12)
+    given.step(12)
+    assert torch.equal(state(auto), state(given))
+    assert auto.status()[0] == given.status()[0] and auto.steps == given.steps == 17
