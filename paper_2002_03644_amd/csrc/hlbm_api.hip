@@ -2,6 +2,7 @@
 // validation, workspace layout, launches and status codes.  The workspace is
 // the caller's device buffer; this file never allocates device memory.
 #include <math.h>
+#include <stddef.h>
 #include <stdlib.h>
 #include <string.h>
 
@@ -194,7 +195,14 @@ void plan_launches(hlbm_handle *h) {
   }
 }
 
-hipError_t run_reduce(hlbm_handle *h, double host[hlbm::kReduceVals], hipStream_t st) {
+// Reduction of the current state, with the status word, which lies kAlign bytes
+// behind the result: one copy and one wait.
+struct Reduced {
+  double v[hlbm::kReduceVals];
+  char pad[kAlign - sizeof(double) * hlbm::kReduceVals];
+  unsigned status;
+};
+hipError_t run_reduce(hlbm_handle *h, Reduced *host, hipStream_t st) {
   hipError_t e;
   const void *state = buf(h, h->cur);
   if (h->p.dtype == HLBM_F64)
@@ -202,8 +210,8 @@ hipError_t run_reduce(hlbm_handle *h, double host[hlbm::kReduceVals], hipStream_
   else
     e = hlbm::f32::reduce(h->dom, state, partials(h), hlbm::kReduceParts, red_out(h), st);
   if (e != hipSuccess) return e;
-  e = hipMemcpyAsync(host, red_out(h), sizeof(double) * hlbm::kReduceVals, hipMemcpyDeviceToHost,
-                     st);
+  static_assert(offsetof(Reduced, status) == kAlign, "status word follows the result");
+  e = hipMemcpyAsync(host, red_out(h), kAlign + sizeof(unsigned), hipMemcpyDeviceToHost, st);
   if (e != hipSuccess) return e;
   return hipStreamSynchronize(st);
 }
@@ -315,18 +323,18 @@ int hlbm_init(hlbm_handle **out, const hlbm_params *p, void *workspace, size_t w
     hipLaunchKernelGGL(k_clear_words, dim3(1), dim3(64), 0, st, status_word(h), 64);
     e = hipGetLastError();
   }
-  double host[hlbm::kReduceVals];
-  if (e == hipSuccess) e = run_reduce(h, host, st);
+  Reduced host;
+  if (e == hipSuccess) e = run_reduce(h, &host, st);
   if (e != hipSuccess) {
     free(h);
     return HLBM_EHIP;
   }
-  if (host[4] != 0.0) {  // non-finite, rho <= 0 or theta <= 0 in the input
+  if (host.v[4] != 0.0) {  // non-finite, rho <= 0 or theta <= 0 in the input
     free(h);
     return HLBM_EINVAL;
   }
   *out = h;
-  return host[5] >= 1.0 ? HLBM_WARN_CFL : HLBM_OK;
+  return host.v[5] >= 1.0 ? HLBM_WARN_CFL : HLBM_OK;
 }
 
 int hlbm_step(hlbm_handle *h, int32_t nsteps, hlbm_stream_t stream) {
@@ -402,24 +410,18 @@ int hlbm_set_populations(hlbm_handle *h, const void *F9, const void *s, hlbm_str
 
 int hlbm_totals(hlbm_handle *h, double *host_out4, hlbm_stream_t stream) {
   if (!h || !host_out4) return HLBM_EINVAL;
-  double host[hlbm::kReduceVals];
-  if (run_reduce(h, host, (hipStream_t)stream) != hipSuccess) return HLBM_EHIP;
-  for (int k = 0; k < 4; ++k) host_out4[k] = host[k];
+  Reduced host;
+  if (run_reduce(h, &host, (hipStream_t)stream) != hipSuccess) return HLBM_EHIP;
+  for (int k = 0; k < 4; ++k) host_out4[k] = host.v[k];
   return HLBM_OK;
 }
 
 int hlbm_status(hlbm_handle *h, double *host_max_cfl, hlbm_stream_t stream) {
   if (!h) return HLBM_EINVAL;
-  hipStream_t st = (hipStream_t)stream;
-  double host[hlbm::kReduceVals];
-  if (run_reduce(h, host, st) != hipSuccess) return HLBM_EHIP;
-  unsigned word = 0;
-  if (hipMemcpyAsync(&word, status_word(h), sizeof(unsigned), hipMemcpyDeviceToHost, st) !=
-          hipSuccess ||
-      hipStreamSynchronize(st) != hipSuccess)
-    return HLBM_EHIP;
-  if (host_max_cfl) *host_max_cfl = host[5];
-  return (host[4] != 0.0 || word != 0u) ? HLBM_EDIVERGED : HLBM_OK;
+  Reduced host;
+  if (run_reduce(h, &host, (hipStream_t)stream) != hipSuccess) return HLBM_EHIP;
+  if (host_max_cfl) *host_max_cfl = host.v[5];
+  return (host.v[4] != 0.0 || host.status != 0u) ? HLBM_EDIVERGED : HLBM_OK;
 }
 
 int hlbm_save_state(hlbm_handle *h, void *dst, hlbm_stream_t stream) {

@@ -281,7 +281,7 @@ hipError_t step_batch2(const void *doms, const long long *offs, const void *item
   a.cconserve = 0;
 #define HLBM_BATCH2_CASE(CW)                                                                 \
   case CW:                                                                                   \
-    hipLaunchKernelGGL(k_step_batch2<CW>, dim3(grid), dim3(step2_threads(CW)), 0, st, a);    \
+    hipLaunchKernelGGL(k_step_batch2<CW>, dim3(grid), dim3(step2_lanes(CW)), 0, st, a);    \
     break;
   if (sizeof(real) == 4) {
     switch (cw) {
@@ -309,18 +309,18 @@ int batch2_blocks_per_cu(int cw) {
   int n = 0;
   hipError_t e = hipErrorInvalidValue;
   if (cw == 64)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_step_batch2<64>, step2_threads(64), 0);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_step_batch2<64>, step2_lanes(64), 0);
   if (cw == 128)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_step_batch2<128>, step2_threads(128),
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_step_batch2<128>, step2_lanes(128),
                                                      0);
   if (cw == 120 && sizeof(real) == 4)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_step_batch2<120>, step2_threads(120),
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_step_batch2<120>, step2_lanes(120),
                                                      0);
   if (cw == 184 && sizeof(real) == 4)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_step_batch2<184>, step2_threads(184),
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_step_batch2<184>, step2_lanes(184),
                                                      0);
   if (cw == 192 && sizeof(real) == 4)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_step_batch2<192>, step2_threads(192),
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_step_batch2<192>, step2_lanes(192),
                                                      0);
   return e == hipSuccess && n > 0 ? n : 1;
 }

@@ -112,21 +112,26 @@ inline TileShape step2_tile(int nx, int ny, int tile_w, int tile_h, int elem_siz
 // latencies).
 constexpr int kModelCUs = 256;
 inline long long sweep_cost(long long nb, int rows, int waves, int per_cu, int steps,
-                            int elem_size) {
-  static const int t_two[] = {145, 173, 178, 186, 232, 240};
+                            int elem_size, bool split = false) {
+  static const int t_split[] = {110, 118, 126, 134, 152, 154, 177, 212};  // two-step, two groups
+  static const int t_two[] = {145, 173, 178, 186, 232, 265};
   static const int t_one32[] = {115, 124, 140, 160, 182, 205, 225, 240, 260, 280, 305, 330};
   static const int t_one64[] = {185, 190, 257, 285, 330, 400};
-  const int *time = steps == 2 ? t_two : (elem_size == 4 ? t_one32 : t_one64);
-  const int last = steps == 2 ? 5 : (elem_size == 4 ? 11 : 5), fill = steps == 2 ? 8 : 4;
-  auto iter = [&](int wgs_per_cu) {  // ceil(2 wgs waves / 4), as an index
-    const int k = (wgs_per_cu * waves + 1) / 2 - 1;
+  const int *time =
+      split ? t_split : (steps == 2 ? t_two : (elem_size == 4 ? t_one32 : t_one64));
+  const int last = split ? 7 : (steps == 1 && elem_size == 4 ? 11 : 5);
+  const int fill = steps == 2 ? 8 : 4;
+  const int resident = kModelCUs * per_cu;
+  auto iter = [&](int wgs) {  // half waves per SIMD of the fullest CUs, as an index
+    int k = ((wgs + kModelCUs - 1) / kModelCUs * waves + 1) / 2 - 1;
+    // four groups' pairs a CU: not yet at its instruction rate while a third of
+    // the CUs hold three
+    if (split && k == last && 10 * wgs <= 9 * resident) --k;
     return time[k > last ? last : k];
   };
-  const int resident = kModelCUs * per_cu;
   const long long rounds = nb < (1 << 30) ? (int)nb / resident : nb / resident;
   const int rest = (int)(nb - rounds * resident);
-  return (rows + fill) *
-         (rounds * iter(per_cu) + (rest ? iter((rest + kModelCUs - 1) / kModelCUs) : 0));
+  return (rows + fill) * (rounds * iter(resident) + (rest ? iter(rest) : 0));
 }
 
 // Tile shape that an automatic launch takes (tile_w and tile_h both left to
@@ -135,8 +140,8 @@ inline long long sweep_cost(long long nb, int rows, int waves, int per_cu, int s
 // round nearly empty: 1500 x 1100 in two-step strips of 184 x 8 is 1242
 // workgroups, a second round of 218.  The shape is the one of least modelled time
 // over all widths and heights.  us per step, nominal -> fitted: FP32 two-step
-// 1500 x 1100 31.0 -> 21.7, 900^2 (one step before) 23.2 -> 15.1, 500^2 11.8 ->
-// 9.7, 200^2 9.9 -> 7.1, 2048^2 55.2 -> 50.4; one-step 2048 x 512 26.8 -> 23.9;
+// 1500 x 1100 31.0 -> 20.9, 900^2 (one step before) 23.2 -> 13.9, 500^2 11.8 ->
+// 9.2, 200^2 9.9 -> 5.9, 2048^2 55.2 -> 50.4; one-step 2048 x 512 26.8 -> 23.9;
 // FP64 600^2 25.8 -> 23.7, 200^2 13.9 -> 11.4.
 //
 // Grids of at least four full rounds of nominal tiles keep those: their rounds
@@ -144,9 +149,11 @@ inline long long sweep_cost(long long nb, int rows, int waves, int per_cu, int s
 // 96 697).
 struct FitShape {
   int bw, waves, per_cu, max_nx;  // width, waves per workgroup, resident workgroups per CU
+  bool split = false;             // two groups of waves (two-step sweep)
 };
 inline TileShape fit_tile(int nx, int ny, const TileShape &nominal, int elem_size, int steps) {
-  static const FitShape two[] = {{64, 2, 6, 64}, {120, 2, 6, 1 << 30}, {184, 3, 4, 1 << 30}};
+  static const FitShape two[] = {
+      {64, 4, 4, 64, true}, {120, 4, 4, 1 << 30, true}, {184, 3, 4, 1 << 30}};
   static const FitShape one32[] = {
       {64, 2, 12, 1 << 30}, {128, 3, 8, 1 << 30}, {192, 4, 6, 1 << 30}, {256, 5, 4, 1 << 30}};
   static const FitShape one64[] = {{64, 2, 6, 1 << 30}, {128, 3, 4, 1 << 30}, {192, 4, 3, 1 << 30}};
@@ -166,8 +173,8 @@ inline TileShape fit_tile(int nx, int ny, const TileShape &nominal, int elem_siz
     if (nx > f.max_nx) continue;
     for (int rows = ny < 2 ? ny : 2; rows <= ny && rows <= 128; rows += rows < 48 ? 1 : 4) {
       const long long cost =
-          sweep_cost(tiles(f.bw, rows), rows, f.waves, f.per_cu, steps, elem_size);
-      if (least < 0 || cost < least) {
+          sweep_cost(tiles(f.bw, rows), rows, f.waves, f.per_cu, steps, elem_size, f.split);
+      if (least < 0 || cost < least || (cost == least && f.bw > best.bw)) {
         least = cost;
         best.bw = f.bw;
         best.rows = rows;

@@ -60,9 +60,12 @@ struct TileRings2 {
   LevelRings<W> L1, L2;
 };
 
-// Threads of a two-step workgroup: the tile's CW columns and the 8 halo
-// columns, rounded up to whole waves.
-constexpr int step2_threads(int cw) { return (cw + 8 + 63) / 64 * 64; }
+// Lanes of a two-step tile: its CW columns and the 8 halo columns, rounded up to
+// whole waves.  Single domains run tiles of 64 and 120 columns split (below): twice
+// as many threads.
+constexpr int step2_lanes(int cw) { return (cw + 8 + 63) / 64 * 64; }
+constexpr bool step2_split(int cw) { return cw == 64 || cw == 120; }
+constexpr int step2_threads(int cw) { return step2_lanes(cw) * (step2_split(cw) ? 2 : 1); }
 
 template <int CW, bool kBatch = false>
 __device__ __forceinline__ void sweep_tile2(const DomainArgs &d, const real *src0, real *dst0,
@@ -170,11 +173,139 @@ __device__ __forceinline__ void sweep_tile2(const DomainArgs &d, const real *src
   if (health.bad() || (c1 && health2.bad())) atomicOr(status, 1u);
 }
 
+// The same sweep by two groups of waves: the first runs level n (loads, A1, B1,
+// C1), the second level n + 1 (A2, B2, C2, stores), half an iteration behind,
+// with level n + 1's rows handed over through LDS.  A wave issues one instruction
+// every four cycles at most, so on grids that leave one or two waves on a SIMD an
+// iteration lasts as long as one wave's instructions for both levels; half of
+// them a wave, on twice the waves, take 1.2 instead of 1.45 us (one workgroup
+// of 120 columns per CU).  us per step, one group -> two: 200^2 7.1 -> 5.9, 500^2
+// 9.7 -> 9.1, 900^2 15.1 -> 13.8, 1500 x 1100 22.4 -> 20.8; level at 2048^2 and
+// 8192^2.  Wider tiles keep one group: the hand-over leaves 184 columns two
+// workgroups per CU instead of four (8192^2 629 -> 764).
+template <int CW>
+struct SplitRings2 {
+  static constexpr int W = CW + 8;
+  LevelRings<W> L1, L2;
+  real over[kPlanes][W];  // a row of level n + 1, from the first group to the second
+};
+
+template <int CW>
+__device__ __forceinline__ void sweep_tile2_split(const DomainArgs &d, const real *src0,
+                                                  real *dst0, unsigned *status, const int rows,
+                                                  const int bx, const int by,
+                                                  SplitRings2<CW> &R) {
+  constexpr int kGroup = step2_lanes(CW);
+  const bool second = __builtin_amdgcn_readfirstlane((int)threadIdx.x >= kGroup);
+  const int t = (int)threadIdx.x - (second ? kGroup : 0);
+  const int x0 = bx * CW, y0 = by * rows;
+  // lane -> ring position: tile lanes at 4..CW+3, halo lanes at 0..3 and CW+4..CW+7
+  const int h = t - CW;
+  const int ri = t < CW ? t + 4 : (h < 4 ? h : (h < 8 ? CW + h : 0));
+  const int vx = x0 - 4 + ri;
+  const int nrow = min(rows, d.ny - y0), last = nrow + 7;
+  constexpr unsigned kEl = sizeof(real);
+  Health health;
+  LevelRegs g;
+  // rows mod 3: m = i mod 3, mp = (i + 1) mod 3
+  int m = 0, mp = 1;
+  auto end_row = [&]() {
+    m = mp;
+    mp = mp == 2 ? 0 : mp + 1;
+    __syncthreads();
+  };
+  if (!second) {
+    const real *src[kPlanes];
+#pragma unroll
+    for (int q = 0; q < kPlanes; ++q) src[q] = src0 + (long long)q * d.plane;
+    const int cx = map_index(vx, d.nx, d.bcx);
+    RowWalk walk(y0 - 4, d.ny, d.bcy);
+    real lda[kPlanes], ldb[kPlanes];  // rows in flight: even and odd ones
+    auto load_row = [&](real (&to)[kPlanes]) {  // the next row
+      const unsigned off = (unsigned)(walk.next(d.ny, d.bcy) * d.pitch + cx) * kEl;
+#pragma unroll
+      for (int q = 0; q < kPlanes; ++q) to[q] = load_at(src[q], off);
+    };
+    auto stage_a = [&](const int z, const real (&ld)[kPlanes]) {
+      real F[kQ];
+#pragma unroll
+      for (int q = 0; q < kQ; ++q) F[q] = ld[q];
+      level_a(d, g, R.L1, z, ri, F, ld[9], health);
+    };
+    // A1(i + 1), B1(i), a barrier, the loads of row i + 3, (kC) C1(i - 1) into the
+    // hand-over, a barrier
+    auto row = [&](const int i, const int z, real (&in)[kPlanes], auto kC) {
+      stage_a(1 - z, in);
+      level_b(d, g, R.L1, z, m, ri, d.sigma, d.sigma1);
+      __syncthreads();
+      if (i + 3 <= nrow + 7) load_row(in);
+      if constexpr (kC.value) {
+        real Fo[kQ], snew;
+        level_c(g, R.L1, 1 - z, mp, ri, Fo, snew);
+#pragma unroll
+        for (int q = 0; q < kQ; ++q) R.over[q][ri] = Fo[q];
+        R.over[9][ri] = snew;
+      }
+      end_row();
+    };
+    load_row(lda);
+    load_row(ldb);
+    stage_a(0, lda);
+    load_row(lda);
+    row(0, 0, ldb, Flag<false>());
+    row(1, 1, lda, Flag<false>());
+    row(2, 0, ldb, Flag<false>());
+    for (int i = 3; i < last;) {
+      row(i, 1, lda, Flag<true>());
+      if (++i == last) break;
+      row(i, 0, ldb, Flag<true>());
+      ++i;
+    }
+    __syncthreads();
+    __syncthreads();
+    if (health.bad()) atomicOr(status, 1u);
+  } else {
+    real *dst[kPlanes];
+#pragma unroll
+    for (int q = 0; q < kPlanes; ++q) dst[q] = dst0 + (long long)q * d.plane;
+    const bool c2 = t < CW && vx < d.nx;
+    // A2(i - 2) from the hand-over, B2(i - 3), a barrier, (kOut) C2(i - 4), a barrier
+    auto row = [&](const int i, auto kOut) {
+      const int z = i & 1;
+      real F[kQ];
+#pragma unroll
+      for (int q = 0; q < kQ; ++q) F[q] = R.over[q][ri];
+      level_a(d, g, R.L2, z, ri, F, R.over[9][ri], health);
+      level_b(d, g, R.L2, 1 - z, m, ri, d.sigma, d.sigma1);
+      __syncthreads();
+      if constexpr (kOut.value) {
+        real Fo[kQ], snew;
+        level_c(g, R.L2, z, mp, ri, Fo, snew);
+        if (c2) {
+          const unsigned off = (unsigned)((y0 + i - 8) * d.pitch + vx) * kEl;
+#pragma unroll
+          for (int q = 0; q < kQ; ++q) store_at(dst[q], off, Fo[q]);
+          store_at(dst[9], off, snew);
+        }
+      }
+      end_row();
+    };
+    for (int i = 0; i < 4; ++i) {
+      __syncthreads();
+      end_row();
+    }
+    for (int i = 4; i < 8; ++i) row(i, Flag<false>());
+    for (int i = 8; i <= last; ++i) row(i, Flag<true>());
+    // level n + 1 is valid on the ring positions that have its stencil
+    if (ri >= 2 && ri <= CW + 5 && health.bad()) atomicOr(status, 1u);
+  }
+}
+
 // Two steps of a whole periodic domain: one workgroup per tile.
 template <int CW>
 __global__ __launch_bounds__(step2_threads(CW))
-__attribute__((amdgpu_waves_per_eu(HLBM_IS_F32 ? 3 : 1))) void k_step2(StepArgs a) {
-  __shared__ TileRings2<CW> R;
+__attribute__((amdgpu_waves_per_eu(HLBM_IS_F32 ? (step2_split(CW) ? 4 : 3) : 1)))
+void k_step2(StepArgs a) {
   int bid = blockIdx.x;
   const int nblk = a.nbx * a.nby;
   if (a.xcd_remap) {
@@ -183,13 +314,20 @@ __attribute__((amdgpu_waves_per_eu(HLBM_IS_F32 ? 3 : 1))) void k_step2(StepArgs 
     const int full = nblk - (per - 1) * 8;
     bid = xcd < full ? xcd * per + k : full * per + (xcd - full) * (per - 1) + k;
   }
-  sweep_tile2<CW>(a.d, a.src, a.dst, a.status, a.rows, bid % a.nbx, bid / a.nbx, 0, R);
+  const int bx = bid % a.nbx, by = bid / a.nbx;
+  if constexpr (step2_split(CW)) {
+    __shared__ SplitRings2<CW> R;
+    sweep_tile2_split<CW>(a.d, a.src, a.dst, a.status, a.rows, bx, by, R);
+  } else {
+    __shared__ TileRings2<CW> R;
+    sweep_tile2<CW>(a.d, a.src, a.dst, a.status, a.rows, bx, by, 0, R);
+  }
 }
 
 // Two steps of a batch of periodic domains: the persistent walk over (domain,
 // tile) items of the one-step batch kernel, with the two-step sweep.
 template <int CW>
-__global__ __launch_bounds__(step2_threads(CW))
+__global__ __launch_bounds__(step2_lanes(CW))
 __attribute__((amdgpu_waves_per_eu(HLBM_IS_F32 ? 3 : 1))) void k_step_batch2(BatchArgs a) {
   __shared__ TileRings2<CW> R;
   const TileWalk walk = tile_walk(a.nitems);
