@@ -496,7 +496,14 @@ int hlbm_restrict(const float *rho, const float *ux, const float *uy, const floa
   a.nx = nx;
   a.f = factor;
   const long long n = (long long)batch * (ny / factor) * (nx / factor);
-  hipLaunchKernelGGL(k_restrict, dim3(grid_for(n, 256)), dim3(256), 0, (hipStream_t)stream, a);
+  // rows of a cell as one load where they are aligned to it (nx is a multiple of the
+  // factor, so the bases decide) and 32-bit cell indices hold with the grid's stride
+  const uintptr_t bases = (uintptr_t)rho | (uintptr_t)ux | (uintptr_t)uy | (uintptr_t)theta;
+  const auto kernel = n >= (1ll << 30) || bases % (4 * (uintptr_t)factor) ? k_restrict
+                      : factor == 4                                      ? k_restrict_rows<4>
+                      : factor == 2                                      ? k_restrict_rows<2>
+                                                                         : k_restrict;
+  hipLaunchKernelGGL(kernel, dim3(grid_for(n, 256)), dim3(256), 0, (hipStream_t)stream, a);
   return hip_status(hipGetLastError());
 }
 

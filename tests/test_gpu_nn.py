@@ -220,6 +220,19 @@ def test_restriction_matches_oracle():
             np.testing.assert_allclose(out[b, c], ref[c], rtol=2e-6, atol=2e-7)
 
 
+@pytest.mark.parametrize("f, nyc, nxc", [(2, 1, 1), (2, 5, 67), (4, 1, 1), (4, 3, 65), (3, 4, 7)])
+def test_restriction_of_unaligned_fields_is_the_same(f, nyc, nxc):
+    """Cell rows are read as one load where the fields' bases allow it: the same
+    bits as from bases one float further, which take the general kernel."""
+    B, ny, nx = 3, nyc * f, nxc * f
+    g = torch.Generator().manual_seed(7)
+    fields = [(torch.rand(B * ny * nx, generator=g) + 0.5).cuda() for _ in range(4)]
+    out = restrict(*[a.view(B, ny, nx) for a in fields], f, batch=B)
+    off = [torch.cat([a[:1], a])[1:].view(B, ny, nx) for a in fields]
+    assert all(a.data_ptr() % 8 for a in off)
+    assert torch.equal(out, restrict(*off, f, batch=B))
+
+
 def closure_batch(count=3, n=64, seed=14):
     params, flds = [], []
     for k in range(count):
