@@ -102,11 +102,11 @@ int batch_steps_per_launch(const hlbm_params *p) {
 }
 
 // Steps per launch of a single domain: as for a batch domain, from
-// kTwoStepMinNodes nodes on.  Smaller grids give the two-step sweep too few
-// workgroups to fill the chip with its taller strips, and the one-step sweep
-// is faster there (MLUPS, one against two steps per launch: 512^2 17.8 k /
-// 13.5 k, 640^2 23.9 / 19.7, 768^2 28.0 / 27.7; 1000^2 35.8 / 38.4, 1024^2
-// 37.3 / 39.9).
+// kTwoStepMinNodes nodes on: what the nominal plan reports.  On its nominal tiles
+// the two-step sweep has too few workgroups on smaller grids (MLUPS, one against
+// two steps per launch, measured on those: 512^2 17.8 k / 13.5 k, 640^2 23.9 /
+// 19.7, 768^2 28.0 / 27.7; 1000^2 35.8 / 38.4, 1024^2 37.3 / 39.9); automatic
+// launches run it there on fitted tiles (see plan_launches).
 constexpr long long kTwoStepMinNodes = 900000;
 int steps_per_launch(const hlbm_params *p) {
   if (p->steps_per_launch) return p->steps_per_launch;

@@ -23,12 +23,15 @@ struct TileShape {
   int xcd_remap; // 0 or 1
 };
 
-// Tile shape of the single-domain step for an nx x ny grid; tile_w, tile_h
-// > 0 are taken as given.
+// Nominal tile shape of the single-domain step for an nx x ny grid; tile_w,
+// tile_h > 0 are taken as given.  Automatic launches of up to a few rounds of
+// workgroups run the shape of fit_tile instead, so the sizes below 2000^2 quoted
+// here, measured on a sweep of six (FP64: two) workgroups per CU, only say what the
+// queries report.
 //  - 192-column tiles with 16-row strips measured fastest at 8192^2 in FP32
 //    (row segments stay 256-byte aligned, the halo wave is a quarter of the
 //    workgroup, 16-row strips beat taller ones).  FP64 (elem_size 8), which
-//    holds two workgroups per CU, runs 2-5 % faster with 32-row strips
+//    held two workgroups per CU then, runs 2-5 % faster with 32-row strips
 //    there.  Grids narrower than 1024 columns keep 128-column tiles with
 //    32-row strips (less ragged); from 1024 columns on, 192 x 8 measured
 //    best or tied in FP32 (1024^2 37.0-37.6 k MLUPS against 35.4-37.3 k for
@@ -55,14 +58,16 @@ inline TileShape step_tile(int nx, int ny, int tile_w, int tile_h, int elem_size
   return t;
 }
 
-// Tile shape of the two-step sweep (periodic domains).  Its workgroup reads a
+// Nominal tile shape of the two-step sweep (periodic domains); as above, fit_tile
+// replaces it on grids of a few rounds.  Its workgroup reads a
 // radius-4 halo, rows + 8 rows for `rows` output rows, so it takes taller
 // strips than the one-step sweep.  FP32 grids from 1024 columns on take
 // 184-column tiles: tile plus halo fill three whole waves (192 columns leave
 // a fourth wave with 8 of 64 lanes busy) and, with the s and theta rings cut
 // to four rows, four workgroups fit a CU's LDS.  At 8192^2 (ms per step):
 // 184 x 64 0.784, x 96 0.791, x 48 0.794, x 32 0.790 against 192 x 64 0.832
-// (0.888 before the rings were cut).  Their strips are the tallest of 64,
+// (0.888 before the rings were cut); with plain stores and two rows of loads in
+// flight 184 x 64 0.631, x 48 0.644, x 96 0.697.  Their strips are the tallest of 64,
 // 32, 16 and 8 rows that give at least 768 workgroups and fill the last
 // round of 1024 resident ones (four per CU on 256 CUs) at least three
 // quarters: best or within 2 % of best at 1024^2 (8 rows), 1500^2 (16),
