@@ -155,8 +155,8 @@ struct ConvArgs {
 // 2), whose accumulators rotate; the next input row and the mask that it
 // needs are loaded while this one's products run, since a wave has nothing else to
 // do (three waves per SIMD).  32 x 256^2, us: 32 -> 32 channels masked 123 -> 90
-// (4.5 TB/s of its two reads and one write), with ReLU 82 -> 70, 32 -> 4 channels
-// 60 -> 54.  For 4 input channels two MFMAs cover the 36 (tap, channel) products of
+// (81 with 16-byte stores, 5.0 TB/s of its two reads and one write), with ReLU 82 ->
+// 70 (68), 32 -> 4 channels 60 -> 54.  For 4 input channels two MFMAs cover the 36 (tap, channel) products of
 // one output row.
 template <int CIN, int NB, int EPI>
 __global__ __launch_bounds__(256) void k_conv(ConvArgs a) {
@@ -173,43 +173,44 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs a) {
   const int xc[3] = {wrap(x0 + n - 1, W), x0 + n, wrap(x0 + n + 1, W)};
   const long long img = (long long)b * H;
 
+  // With two blocks, row 4 j + r of block nb is channel 8 j + 4 nb + r: a lane then
+  // has eight channels in a row, one 16-byte store (and mask load) per pixel instead
+  // of two 8-byte ones 32 bytes apart, each half of a line (4 -> 32 channels, us at
+  // 32 x 256^2: masked 59 -> 52, with ReLU 42 -> 35).
+  // `frag` finds a lane's row of a block in the packed fragments, whose blocks hold 16
+  // channels in order.
+  auto frag = [&](int nb) {
+    if constexpr (NB != 2) return nb * 64 + lane;
+    const int co = 8 * (n >> 2) + 4 * nb + (n & 3);
+    return (co >> 4) * 64 + (lane & 48) + (co & 15);
+  };
+
   f32x4 init[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int co = 16 * nb + 4 * g + r;
+      const int co = NB == 2 ? 8 * g + 4 * nb + r : 4 * g + r;
       init[nb][r] = (EPI != kEpiMask && (EPI != kEpiOut || co < kOut)) ? a.bias[co] : 0.f;
     }
   }
 
   // the ReLU mask of the lane's outputs in row yo
-  auto load_mask = [&](bf16x4 *mk, int yo) {
-    if constexpr (EPI == kEpiMask) {
-      const long long p = (img + yo) * W + x0 + n;
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
-        mk[nb] = *(const bf16x4 *)(a.mask + p * kHid + 16 * nb + 4 * g);
-    }
+  auto load_mask = [&](bf16x8 &mk, int yo) {
+    if constexpr (EPI == kEpiMask)
+      mk = *(const bf16x8 *)(a.mask + ((img + yo) * W + x0 + n) * kHid + 8 * g);
   };
-  auto epilogue = [&](const f32x4 *acc, const bf16x4 *mk, int yo) {
+  auto epilogue = [&](const f32x4 *acc, const bf16x8 &mk, int yo) {
     const long long p = (img + yo) * W + x0 + n;
-    if constexpr (EPI == kEpiRelu) {
+    if constexpr (EPI != kEpiOut) {
+      static_assert(NB == 2, "32 output channels");
+      bf16x8 v;
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        bf16x4 v;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = (bf16)fmaxf(acc[nb][r], 0.f);
-        *(bf16x4 *)(a.out + p * kHid + 16 * nb + 4 * g) = v;
+      for (int k = 0; k < 8; ++k) {
+        const float o = acc[k >> 2][k & 3];
+        v[k] = (bf16)(EPI == kEpiRelu ? fmaxf(o, 0.f) : (float)mk[k] > 0.f ? o : 0.f);
       }
-    } else if constexpr (EPI == kEpiMask) {
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        bf16x4 v;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = (bf16)((float)mk[nb][r] > 0.f ? acc[nb][r] : 0.f);
-        *(bf16x4 *)(a.out + p * kHid + 16 * nb + 4 * g) = v;
-      }
+      *(bf16x8 *)(a.out + p * kHid + 8 * g) = v;
     } else {
       if (g == 0) {
         if (a.osb == 0) {
@@ -231,13 +232,13 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs a) {
 #pragma unroll
     for (int t = 0; t < 9; ++t)
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) wf[t][nb] = a.wp[(t * NB + nb) * 64 + lane];
+      for (int nb = 0; nb < NB; ++nb) wf[t][nb] = a.wp[t * NB * 64 + frag(nb)];
     f32x4 a_prev[NB], a_cur[NB], a_next[NB];
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) a_prev[nb] = a_cur[nb] = a_next[nb] = init[nb];
     // row i of the strip's input, and the mask of the output row that it completes
     bf16x8 bx[3], bx_next[3];
-    bf16x4 mk[NB], mk_next[NB];
+    bf16x8 mk = {}, mk_next = {};
     auto load = [&](int i) {
       const int yin = wrap(y0 - 1 + i, H);
       const bf16 *row = a.in + (img + yin) * W * (long long)kHid + 8 * g;
@@ -250,8 +251,7 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs a) {
     for (int i = 0; i < R + 2; ++i) {
 #pragma unroll
       for (int dx = 0; dx < 3; ++dx) bx[dx] = bx_next[dx];
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) mk[nb] = mk_next[nb];
+      mk = mk_next;
       load(min(i + 1, R + 1));
       if (i < R) {
 #pragma unroll
@@ -286,9 +286,9 @@ __global__ __launch_bounds__(256) void k_conv(ConvArgs a) {
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb) wf[j][nb] = a.wp[(j * NB + nb) * 64 + lane];
+      for (int nb = 0; nb < NB; ++nb) wf[j][nb] = a.wp[j * NB * 64 + frag(nb)];
     for (int yo = y0; yo < y0 + R; ++yo) {
-      bf16x4 mk[NB];
+      bf16x8 mk = {};
       load_mask(mk, yo);
       f32x4 acc[NB];
 #pragma unroll
