@@ -191,7 +191,11 @@ int hlbm_init(hlbm_handle **out, const hlbm_params *p, void *workspace, size_t w
  * that arrived from the interior; F = f^eq(rho_w, (wall_ux, 0), wall_theta) +
  * f^1[a1FD] with the velocity gradient zero along the wall and one-sided
  * second order across it, (-3 u_w + 4 u_1 - u_2) / 2; s from rho_w and
- * wall_theta.  The collision at wall nodes uses sigma = 1. */
+ * wall_theta.  The collision at wall nodes uses sigma = 1.
+ * Under stream capture a call that ends in the state buffer it began in can be
+ * replayed, each replay going on from the state the last one left: calls of an
+ * even number of steps, of a multiple of four where hlbm_launch_plan reports two
+ * steps per launch (hlbm_steps_done counts the captured call once). */
 int hlbm_step(hlbm_handle *h, int32_t nsteps, hlbm_stream_t stream);
 
 /* Write the macroscopic fields of the current state: rho = sum F,

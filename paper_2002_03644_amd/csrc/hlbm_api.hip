@@ -195,6 +195,16 @@ void plan_launches(hlbm_handle *h) {
   }
 }
 
+// Whether work on `st` is being recorded into a graph.  A captured hlbm_step of an
+// even number of steps is replayed as steps of its own where each step is a launch:
+// it ends in the buffer that it began in.  Domains that the nominal plan steps one
+// by one keep that where they take two steps per launch: an odd pair then runs as
+// two single steps (the same bits).
+bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  return st && hipStreamIsCapturing(st, &s) == hipSuccess && s == hipStreamCaptureStatusActive;
+}
+
 // Reduction of the current state, with the status word, which lies kAlign bytes
 // behind the result: one copy and one wait.
 struct Reduced {
@@ -342,18 +352,23 @@ int hlbm_step(hlbm_handle *h, int32_t nsteps, hlbm_stream_t stream) {
   hipStream_t st = (hipStream_t)stream;
   int32_t n = 0;
   while (h->resident && n < nsteps) {
+    // an even number of steps stays in its buffer (the workgroup has read all of
+    // it before it writes), as it does with one launch per step
     const int32_t k = std::min(nsteps - n, hlbm::kResidentSteps);
+    const int to = h->cur ^ (k & 1);
     const hipError_t e =
         h->p.dtype == HLBM_F64
-            ? hlbm::f64::resident(h->dom, buf(h, h->cur), buf(h, h->cur ^ 1), status_word(h), k, st)
-            : hlbm::f32::resident(h->dom, buf(h, h->cur), buf(h, h->cur ^ 1), status_word(h), k, st);
+            ? hlbm::f64::resident(h->dom, buf(h, h->cur), buf(h, to), status_word(h), k, st)
+            : hlbm::f32::resident(h->dom, buf(h, h->cur), buf(h, to), status_word(h), k, st);
     if (e != hipSuccess) return HLBM_EHIP;
-    h->cur ^= 1;
+    h->cur = to;
     h->steps += k;
     n += k;
   }
   if (h->spl == 2) {  // periodic domains, no walls
-    for (; n + 2 <= nsteps; n += 2) {
+    int32_t pairs = (nsteps - n) / 2;
+    if (steps_per_launch(&h->p) == 1 && capturing(st)) pairs &= ~1;
+    for (; pairs > 0; --pairs, n += 2) {
       hipError_t e =
           h->p.dtype == HLBM_F64
               ? hlbm::f64::step2(h->dom, buf(h, h->cur), buf(h, h->cur ^ 1), status_word(h),

@@ -24,7 +24,7 @@ constexpr int kResidentThreads = 512;
 struct ResidentArgs {
   DomainArgs d;
   const real *src;
-  real *dst;
+  real *dst;           // may be src: a thread reads and writes its own nodes only
   unsigned *status;
   int steps, next;  // next: extended nodes
 };

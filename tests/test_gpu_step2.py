@@ -166,3 +166,30 @@ def test_resident_domain_equals_sweeps(nx, ny, opts, dt):
     given.step(12)
     assert torch.equal(state(auto), state(given))
     assert auto.status()[0] == given.status()[0] and auto.steps == given.steps == 17
+
+
+@pytest.mark.parametrize("nx,ny,steps,opts", [
+    (200, 200, 2, dict(dtype="f32")), (200, 200, 6, dict(dtype="f32")),
+    (200, 200, 4, dict(dtype="f32")), (1024, 1024, 4, dict(dtype="f32")),
+    (20, 30, 2, dict(dtype="f32")), (20, 30, 6, dict(dtype="f64")),
+    (2, 100, 2, dict(dtype="f64", bc_y="wall", wall_theta=0.2, wall_ux_hi=0.05)),
+    (200, 64, 2, dict(dtype="f64")),
+])
+def test_captured_even_steps_replay_onwards(nx, ny, steps, opts):
+    """A captured call of an even number of steps (of four where the nominal
+    plan takes two steps per launch) goes on from the last replay's state, with
+    eager steps between the replays."""
+    f = hi.random_smooth(nx, ny, seed=nx + ny + steps, amp=0.03, u0=(0.12, -0.08))
+    p = Params(nx, ny, mu=2e-3, sigma=0.3, **opts)
+    G, E = run(p, f, 4), run(p, f, 4)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        G.step(steps)
+    for k in range(3):
+        graph.replay()
+        E.step(steps)
+        assert torch.equal(state(G), state(E)), k
+        G.step(4)
+        E.step(4)
+        assert torch.equal(state(G), state(E)), k
