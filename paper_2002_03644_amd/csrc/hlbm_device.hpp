@@ -126,6 +126,14 @@ __device__ __forceinline__ double rcp_fast(double x) {
   r = __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
   return __builtin_fma(__builtin_fma(-x, r, 1.0), r, r);
 }
+// A quotient takes as many: one step on the seed and one on the quotient's own
+// residual, which leaves its rounding alone (half a unit; times rcp_fast, 1.5).
+__device__ __forceinline__ double div_fast(double a, double b) {
+  double r = __builtin_amdgcn_rcp(b);
+  r = __builtin_fma(__builtin_fma(-b, r, 1.0), r, r);
+  const double q = a * r;
+  return __builtin_fma(__builtin_fma(-b, q, a), r, q);
+}
 __device__ __forceinline__ float div_fast(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
 __device__ __forceinline__ float exp_r(float x) { return __expf(x); }
 __device__ __forceinline__ double exp_r(double x) { return exp(x); }
@@ -234,22 +242,28 @@ __device__ __forceinline__ double fma_const(double a, double b, const double c, 
 // to 60 instructions for theta, and without library constants held across the
 // row loop and the library's second, precise-theta branch it needs 153 vector
 // registers instead of 208: three waves per SIMD.  2048^2 164 -> 152 us per step,
-// Couette 2 x 100 15.6 -> 13.6; theta over rho = e^-8 .. e^8 is 10.5 units of 2^-53
-// off at most (14.4 before), 1.0 near rho = 1, s = 0 (1.0).
-//
+// Couette 2 x 100 15.6 -> 13.6.  theta over rho = e^-8 .. e^8, s = -1 .. 1 is at
+// most 7.5 units of 2^-53 off, 1.0 near rho = 1 and s = 0, as with the library's
+// (the argument's rounding).
+
+// ln 2 = hi + lo, hi with 21 trailing zero bits: k hi is exact for |k| < 2^11.
+constexpr double kLn2Hi = 0x1.62e42feep-1, kLn2Lo = 0x1.a39ef35793c76p-33;
+
 // ln x of a positive normal number, x = 2^k m with m in [sqrt(1/2), sqrt(2)):
-// k ln 2 + 2 atanh(t), t = (m - 1) / (m + 1), by the series of atanh to t^21 (|t| <
-// 0.172: truncated below 2^-56 of t).  Within 1.5 units in the last place.
+// k ln 2 + 2 atanh(t), t = f / (2 + f), f = m - 1, by the series of atanh to t^21
+// (|t| < 0.172: truncated below 2^-56 of t).  With 2 t = f - t f the leading term
+// is f itself, which is exact, and t's own rounding only enters times f: within
+// 1.2 units in the last place (0.9 measured; 2.0 with 2 t for the leading term and
+// ln 2 in one part).  Anything else (zero, negative, infinite) gives no meaningful
+// number; the density it is taken of flags the state.
 __device__ __forceinline__ double log_near(double x, const int zero) {
   double m = __builtin_amdgcn_frexp_mant(x);  // [1/2, 1)
   int k = __builtin_amdgcn_frexp_exp(x);
   const bool low = m < 0.70710678118654752440;
   m = low ? m + m : m;
   k = low ? k - 1 : k;
-  const double f = m - 1.0, den = m + 1.0;
-  const double r = rcp_fast(den);
-  double t = f * r;
-  t = __builtin_fma(__builtin_fma(-t, den, f), r, t);
+  const double f = m - 1.0;
+  const double t = f * rcp_fast(m + 1.0);
   const double z = t * t;
   double p = near_const(2.0 / 21.0, zero);
   p = fma_const(p, z, 2.0 / 19.0, zero);
@@ -261,19 +275,21 @@ __device__ __forceinline__ double log_near(double x, const int zero) {
   p = fma_const(p, z, 2.0 / 7.0, zero);
   p = fma_const(p, z, 2.0 / 5.0, zero);
   p = fma_const(p, z, 2.0 / 3.0, zero);
-  const double log_m = __builtin_fma(t * z, p, t + t);
-  return __builtin_fma((double)k, near_const(0.69314718055994530942, zero), log_m);
+  const double e = (double)k, hi = near_const(kLn2Hi, zero);
+  const double sum = __builtin_fma(e, hi, f);
+  const double lost = __builtin_fma(e, hi, -sum) + f;  // its rounding, exactly
+  const double low_part = __builtin_fma(e, near_const(kLn2Lo, zero), lost);
+  return sum + __builtin_fma(-t, __builtin_fma(-z, p, f), low_part);
 }
 
 // e^x - off, off 0 or 1: 2^k + 2^k (e^r - 1) - off with k = round(x / ln 2), |r|
 // <= ln 2 / 2 in two parts of ln 2 and e^r - 1 by the Taylor series to r^13
 // (truncated below 2^-57), so off = 1 is accurate relative to itself (expm1).
+// Within 1.1 units in the last place (1.0 measured).
 __device__ __forceinline__ double exp_near(double x, const double off, const int zero) {
   const double k = __builtin_rint(x * near_const(1.44269504088896340736, zero));
-  // ln 2 = hi + lo, hi with 32 trailing zero bits, so k hi is exact
-  constexpr double hi = 0x1.62e42feep-1, lo = 0x1.a39ef35793c76p-33;
-  double r = __builtin_fma(-k, near_const(hi, zero), x);
-  r = __builtin_fma(-k, near_const(lo, zero), r);
+  double r = __builtin_fma(-k, near_const(kLn2Hi, zero), x);
+  r = __builtin_fma(-k, near_const(kLn2Lo, zero), r);
   double p = near_const(1.0 / 6227020800.0, zero);
   p = fma_const(p, r, 1.0 / 479001600.0, zero);
   p = fma_const(p, r, 1.0 / 39916800.0, zero);
@@ -346,7 +362,7 @@ __device__ __forceinline__ real tiny_sq() { return sizeof(real) == 4 ? real(1e-3
 __device__ __forceinline__ real van_albada(real a, real b) {
   const real ab = a * b;
   const real den = fma_r(a, a, b * b);
-  return (ab > real(0) && den > tiny_sq()) ? (ab * (a + b)) * rcp_fast(den) : real(0);
+  return (ab > real(0) && den > tiny_sq()) ? div_fast(ab * (a + b), den) : real(0);
 }
 
 // Upwind MUSCL derivative u ds/dx at a node from the four differences around it,
@@ -362,7 +378,7 @@ __device__ __forceinline__ real muscl(real u, real dmm, real dm, real dp, real d
 
 // Fourier and viscous heat over rho theta.
 __device__ __forceinline__ real heat_term(const DomainArgs &d, real lap, real phi, real pt) {
-  return fma_r(d.lambda, lap, phi) * rcp_fast(pt);
+  return div_fast(fma_r(d.lambda, lap, phi), pt);
 }
 
 // Laplacian of theta (or of theta - theta_ref, the same).
@@ -412,7 +428,7 @@ __device__ __forceinline__ NodeState node_state(const DomainArgs &d, const real 
   }
 #else
   const int zero = opaque_zero();
-  o.lapv = exp_near(fma_r(sv, d.inv_cv, d.gm1 * log_near(m.rho, zero)), d.th_off, zero);
+  o.lapv = exp_near(sv * d.inv_cv + d.gm1 * log_near(m.rho, zero), d.th_off, zero);
   th = o.lapv + d.th_off;
 #endif
   const real omt = real(1) - th;
