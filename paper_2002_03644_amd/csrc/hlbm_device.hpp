@@ -57,8 +57,8 @@ struct DomainArgs {
   real th_off;         // theta - lapv: theta_ref with the precise-theta flag, else 0
   real eps_u;          // sgn_eps, infinite for the centred E1
   real sigma1;         // 1 - sigma
-  real half_mu, mu9;   // mu / 2, mu / 9
-  real e2h, e2k;       // E2's factor: (2 - gamma) / 2, and times cs2 / 18; zero without E2
+  real half_mu;        // mu / 2
+  real e2h, e2k;       // E2's factor: (2 - gamma) / 2, and times cs2 / 2; zero without E2
   real cref;           // cs2 (theta_ref - 1)
   real k4;             // 9 / 4, zero for the third-order expansion
 };
@@ -468,9 +468,13 @@ __device__ __forceinline__ real upwind_gamma(const DomainArgs &d, real u, real g
 //     b = (1 - 1/taubar) a1:
 //       Axxy  = uy (rho ux^2 + rho c + bxx) + 2 ux bxy,
 //       Axxyy = Y (rho ux^2 + bxx) + X byy + rho c uy^2 + 4 ux uy bxy + rho c^2;
-//   - every coefficient carries the factor 1/9 of the projection from the
-//     start (rho / 9, (1 - 1/taubar) / 9, ...), which leaves the projection
-//     factors that are exact in binary.
+//   - the populations along an axis are summed from the terms that cancel first
+//     (rho + 3 Axx), so that no partial sum is larger than it has to be, and
+//     multiplied by their weight last.  With the factor 1/9 carried from the start
+//     and one sum for both axes (15 instructions of 250 less, 1 % of the time at
+//     1500 x 1100, none at 4096^2) a step rounded more than the formulas as they
+//     stand: velocities 2 to 4 % further from 80-bit ones, 7 % from 64-bit ones at
+//     2048^2; this way 3 to 5 % closer, and level.
 // FP32: deviations from the rest reference formed from deviations (p - p_ref,
 // rho c - rho_ref c_ref, rho c^2 - rho_ref c_ref^2).  Its rounding is kept term
 // by term: E1 is discontinuous in the sign of u, so where a velocity crosses
@@ -536,7 +540,7 @@ __device__ __forceinline__ void collide(const DomainArgs &d, const NodeState &o,
   }
   pt = rho * th;
 #else
-  constexpr real cs2 = real(kCs2), c9 = real(1.0 / 9.0);
+  constexpr real cs2 = real(kCs2);
   const real ux = o.ux, uy = o.uy;
   const real th = o.lapv + d.th_off;
   const real rho = o.dr;
@@ -547,63 +551,62 @@ __device__ __forceinline__ void collide(const DomainArgs &d, const NodeState &o,
   pt = rho * th;
   const real tp = fma_r(pt, real(0.5 * kCs2), d.mu);
   const real rtp = rcp_fast(tp);
-  const real om9 = fma_r(pt, real(-0.5 * kCs2 / 9.0), d.mu9) * rtp;
-  const real c = fma_r(th, cs2, -cs2);
-  const real rho9 = rho * c9;
-  const real rc9 = rho9 * c;
-  const real dp9 = real(kCs2 / 9.0) * pt;
-  // (E1 + E2) / 18
+  const real om = fma_r(pt, real(-0.5 * kCs2), d.mu) * rtp;
+  const real c = cs2 * (th - real(1));
+  const real rc = rho * c;
+  const real dp = cs2 * pt;
+  // (E1 + E2) / 2
   const real e1x = upwind_gamma(d, ux, n.gxw, n.gxc, n.gxe);
   const real e1y = upwind_gamma(d, uy, n.gys, n.gyc, n.gyn);
   const real e2 = d.e2k * (pt * (gxx + gyy));
-  const real hEx = fma_r(e1x, real(0.5 / 9.0), e2);
-  const real hEy = fma_r(e1y, real(0.5 / 9.0), e2);
-  const real rux = rho9 * ux, ruy = rho9 * uy;
+  const real hEx = fma_r(e1x, real(0.5), e2);
+  const real hEy = fma_r(e1y, real(0.5), e2);
+  const real rux = rho * ux, ruy = rho * uy;
   const real uxx = ux * ux, uyy = uy * uy;
-  const real ruxx = rho9 * uxx, ruyy = rho9 * uyy, ruxy = rux * uy;
+  const real ruxx = rux * ux, ruyy = ruy * uy, ruxy = rux * uy;
   // HRR stress
   const real fd = sg1 * fma_r(pt, real(-0.25 * kCs2), -d.half_mu);
   const real fS = fd * S, fT = fd * T;
-  const real prxx = fma_r(real(-9), (dp9 + ruxx) - hEx, o.pxx);
-  const real pryy = fma_r(real(-9), (dp9 + ruyy) - hEy, o.pyy);
-  const real prxy = fma_r(real(-9), ruxy, o.pxy);
+  const real prxx = o.pxx - ((dp + ruxx) - hEx);
+  const real pryy = o.pyy - ((dp + ruyy) - hEy);
+  const real prxy = o.pxy - ruxy;
   const real axx = fma_r(sg, prxx, fS), ayy = fma_r(sg, pryy, -fS), axy = fma_r(sg, prxy, fT);
   if (d.flags & kFlagPhiFD) {
     phi = (real(0.5) * d.half_mu) * fma_r(S, S, T * T);
   } else {
     phi = -(d.half_mu * rtp) * fma_r(axx, gxx, fma_r(axy, T, ayy * gyy));
   }
-  const real bxx = om9 * axx, byy = om9 * ayy, bxy = om9 * axy;
+  const real bxx = om * axx, byy = om * ayy, bxy = om * axy;
   const real Nx = ruxx + bxx, Ny = ruyy + byy;
-  const real Axx = Nx + (rc9 + hEx), Ayy = Ny + (rc9 + hEy), Axy = ruxy + bxy;
+  const real Axx = (ruxx + rc) + (bxx + hEx), Ayy = (ruyy + rc) + (byy + hEy), Axy = ruxy + bxy;
   const real ux2 = ux + ux, uy2 = uy + uy;
   const real P1 = ux2 * bxy, P2 = uy2 * bxy;
-  const real Axxy = fma_r(uy, Nx + rc9, P1), Axyy = fma_r(ux, Ny + rc9, P2);
+  const real Axxy = fma_r(uy, Nx + rc, P1), Axyy = fma_r(ux, Ny + rc, P2);
   const real X = uxx + c, Y = uyy + c;
   const real Axxyy =
-      fma_r(Y, Nx, fma_r(rc9, uyy, fma_r(X, byy, fma_r(uy2, P1, rc9 * c))));
+      fma_r(Y, Nx, fma_r(rc, uyy, fma_r(X, byy, fma_r(uy2, P1, rc * c))));
   // projection on the nine populations
+  constexpr real w0 = real(4.0 / 9.0), w1 = real(1.0 / 9.0), w2 = real(1.0 / 36.0);
   const real s = Axx + Ayy;
   const real Z = d.k4 * Axxyy;
-  const real W = fma_r(real(-1.5), s, rho9);
-  f[0] = real(4) * (W + Z);
-  const real v = fma_r(real(-2), Z, W);
-  const real px = fma_r(real(4.5), Axx, v), py = fma_r(real(4.5), Ayy, v);
-  const real ox = fma_r(real(-4.5), Axyy, real(3) * rux);
-  const real oy = fma_r(real(-4.5), Axxy, real(3) * ruy);
-  f[1] = px + ox;
-  f[3] = px - ox;
-  f[2] = py + oy;
-  f[4] = py - oy;
-  const real bd = fma_r(real(0.75), s, fma_r(real(0.25), rho9, Z));
-  const real dxy = real(2.25) * Axy;
-  const real dx = fma_r(real(2.25), Axyy, real(0.75) * rux);
-  const real dy = fma_r(real(2.25), Axxy, real(0.75) * ruy);
+  f[0] = w0 * (fma_r(real(-1.5), s, rho) + Z);
+  const real px = fma_r(real(-1.5), Ayy, fma_r(real(-2), Z, fma_r(real(3), Axx, rho)));
+  const real py = fma_r(real(-1.5), Axx, fma_r(real(-2), Z, fma_r(real(3), Ayy, rho)));
+  const real ox = fma_r(real(3), rux, real(-4.5) * Axyy);
+  const real oy = fma_r(real(3), ruy, real(-4.5) * Axxy);
+  f[1] = w1 * (px + ox);
+  f[3] = w1 * (px - ox);
+  f[2] = w1 * (py + oy);
+  f[4] = w1 * (py - oy);
+  const real bd = fma_r(real(3), s, fma_r(real(4), Z, rho));
+  const real dxy = real(9) * Axy;
+  const real dx = fma_r(real(3), rux, real(9) * Axyy);
+  const real dy = fma_r(real(3), ruy, real(9) * Axxy);
   const real ep = bd + dxy, em = bd - dxy, gp = dx + dy, gm = dx - dy;
-  f[5] = ep + gp;
-  f[7] = ep - gp;
-  f[6] = em - gm;
-  f[8] = em + gm;
+  f[5] = w2 * (ep + gp);
+  f[7] = w2 * (ep - gp);
+  f[6] = w2 * (em - gm);
+  f[8] = w2 * (em + gm);
 #endif
 }
 

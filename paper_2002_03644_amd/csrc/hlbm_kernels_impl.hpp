@@ -36,9 +36,8 @@ static DomainArgs to_device(const HostDomain &h) {
   d.eps_u = (h.flags & kFlagE1Centred) ? (real)__builtin_inf() : d.sgn_eps;
   d.sigma1 = real(1) - d.sigma;
   d.half_mu = (real)(h.mu * 0.5);
-  d.mu9 = (real)(h.mu / 9.0);
   d.e2h = (h.flags & kFlagE2Off) ? real(0) : d.e2c * real(0.5);
-  d.e2k = (h.flags & kFlagE2Off) ? real(0) : (real)(h.e2c * kCs2 / 36.0);
+  d.e2k = (h.flags & kFlagE2Off) ? real(0) : (real)(h.e2c * kCs2 / 4.0);
   d.cref = real(kCs2) * (d.theta_ref - real(1));
   d.k4 = (h.flags & kFlagFeq3) ? real(0) : real(2.25);
   return d;
