@@ -187,7 +187,7 @@ __global__ __launch_bounds__(256) void k_batch_moments(BatchFieldArgs a) {
     if (a.ux) a.ux[fo + i] = m.jx / m.rho;
     if (a.uy) a.uy[fo + i] = m.jy / m.rho;
     if (a.s) a.s[fo + i] = sv + d.s_ref;
-    if (a.theta) a.theta[fo + i] = node_theta(m.rho, sv, d);
+    if (a.theta) a.theta[fo + i] = field_theta(m.rho, sv, d);
   }
 }
 

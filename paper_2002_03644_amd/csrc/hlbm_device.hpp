@@ -53,7 +53,7 @@ struct DomainArgs {
   real rho_ref, theta_ref, log_rho_ref, s_ref;
   real fref[kQ];       // deviation reference populations (zero in the FP64 form)
   real wall_u_lo, wall_u_hi, wall_theta;  // bcy == kBcWall: wall velocities, temperature
-  // constants of the step formed once on the host (see node_theta and collide)
+  // constants of the step formed once on the host (see node_state and collide)
   real th_off;         // theta - lapv: theta_ref with the precise-theta flag, else 0
   real eps_u;          // sgn_eps, infinite for the centred E1
   real sigma1;         // 1 - sigma
@@ -205,8 +205,9 @@ __device__ __forceinline__ NodeMoments node_moments(const real F[kQ], const Doma
 }
 
 // Natural logarithm of a normal number from the hardware's base-two one, the
-// product with ln 2 = hi + lo kept to the last bit.  Zero and infinity give NaN
-// (the densities it is taken of flag the state then either way).
+// product with ln 2 = hi + lo kept to the last bit: the three operations that the
+// open AMDGPU back end of LLVM lowers log to, without what it adds for zero and
+// infinity, which give NaN here (such a density flags the state either way).
 __device__ __forceinline__ float log_normal(float x) {
   const float y = __builtin_amdgcn_logf(x);
   constexpr float hi = 0x1.62e42ep-1f, lo = 0x1.efa39ep-25f;
@@ -308,14 +309,11 @@ __device__ __forceinline__ double exp_near(double x, const double off, const int
 }
 #endif
 
-// theta from the stored entropy (deviation form: ds = s - s_ref).
-__device__ __forceinline__ real node_theta(real rho, real sv, const DomainArgs &d) {
-#if HLBM_IS_F32
-  return d.theta_ref * exp_r(sv * d.inv_cv + d.gm1 * (log_normal(rho) - d.log_rho_ref));
-#else  // theta_ref = 1, log_rho_ref = 0 here
-  const int zero = opaque_zero();
-  return exp_near(fma_r(sv, d.inv_cv, d.gm1 * log_near(rho, zero)), 0.0, zero);
-#endif
+// theta from the stored entropy (deviation form: ds = s - s_ref), as the fields and
+// reductions give it: any density has the value the functions give it (zero 0,
+// negative NaN, infinite infinite), in FP64 with the library's.
+__device__ __forceinline__ real field_theta(real rho, real sv, const DomainArgs &d) {
+  return d.theta_ref * exp_r(sv * d.inv_cv + d.gm1 * (log_r(rho) - d.log_rho_ref));
 }
 
 // theta - theta_ref with relative accuracy on the deviation itself:
@@ -424,7 +422,7 @@ __device__ __forceinline__ NodeState node_state(const DomainArgs &d, const real 
     o.lapv = node_dtheta(m.dr, m.rho, sv, d);
     th = o.lapv + d.th_off;
   } else {
-    th = o.lapv = node_theta(m.rho, sv, d);
+    th = o.lapv = d.theta_ref * exp_r(sv * d.inv_cv + d.gm1 * (log_normal(m.rho) - d.log_rho_ref));
   }
 #else
   const int zero = opaque_zero();
@@ -1189,7 +1187,7 @@ __global__ void k_moments(FieldArgs a) {
     if (a.ux) a.ux[i] = m.jx / m.rho;
     if (a.uy) a.uy[i] = m.jy / m.rho;
     if (a.s) a.s[i] = sv + d.s_ref;
-    if (a.theta) a.theta[i] = node_theta(m.rho, sv, d);
+    if (a.theta) a.theta[i] = field_theta(m.rho, sv, d);
   }
 }
 
@@ -1257,7 +1255,7 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce(ReduceArgs a) {
     const NodeMoments m = node_moments(F, d);
     const double rho = (double)m.rho;
     const double ux = (double)m.jx / rho, uy = (double)m.jy / rho;
-    const double th = (double)node_theta(m.rho, sv, d);
+    const double th = (double)field_theta(m.rho, sv, d);
     acc[0] += rho;
     acc[1] += (double)m.jx;
     acc[2] += (double)m.jy;

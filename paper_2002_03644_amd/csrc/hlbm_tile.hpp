@@ -291,13 +291,15 @@ __device__ __forceinline__ void tile_c_store(const DomainArgs &d, real *dst0, co
 #pragma unroll
     for (int q = 0; q < kQ; ++q) store_stream(dst0 + (long long)q * d.plane, off, Fo[q]);
     store_stream(dst0 + 9LL * d.plane, off, snew);
-    if (mom) {  // the arithmetic of k_batch_moments on the values just stored
+    // the arithmetic of k_batch_moments on the values just stored (the corrected
+    // cycle, which is FP32)
+    if (HLBM_IS_F32 && mom) {
       const NodeMoments m = node_moments(Fo, d);
       const long long i = (long long)y * d.nx + x;
       mom[i] = m.rho;
       mom[mom_sc + i] = m.jx / m.rho;
       mom[2 * mom_sc + i] = m.jy / m.rho;
-      mom[3 * mom_sc + i] = node_theta(m.rho, snew, d);
+      mom[3 * mom_sc + i] = field_theta(m.rho, snew, d);
     }
   }
 }

@@ -322,3 +322,32 @@ def test_f32_sod_tolerance():
     A.step(1900)
     B.step(1900)
     check_tol("sod2000", gpu_moments(A), gpu_moments(B), ("rho", "ux", "s"))
+
+
+@pytest.mark.parametrize("dt", ["f64", "f32"])
+def test_theta_of_any_density(dt):
+    """theta = rho^(gamma - 1) exp(s / c_v) of the fields, also where no flow gets:
+    zero, negative, subnormal and infinite densities, entropies past the
+    exponential's range (FP32: those whose deviation form is exact)."""
+    inf = float("inf")
+    rho = [1.0, 0.7, 3.0, -1.0, inf, 1.0, 1.0]
+    s = [-1.0, 0.2, 0.5, 0.1, 0.1, inf, -inf]
+    if dt == "f64":
+        rho += [0.0, 1e-310, 1e300, 1.0, 1.0, 1.0]
+        s += [0.3, -1.0, 0.1, 591.25, 600.0, -640.0]
+    td = torch.float64 if dt == "f64" else torch.float32
+    n = len(rho)
+    one = np.ones((1, n))
+    S = Solver(Params(n, 1, dtype=dt), one, 0 * one, 0 * one, theta=0.2 * one)
+    F = torch.zeros(9, 1, n, dtype=td)
+    F[0, 0] = torch.tensor(rho, dtype=td)
+    sv = torch.tensor(s, dtype=td)[None]
+    S.set_populations(F, sv)
+    got = S.moments()["theta"].cpu().double()[0]
+    cv = (1.0 / 3.0) / 0.4
+    want = torch.exp(sv[0].double() / cv + 0.4 * torch.log(F[0, 0].double()))
+    # the argument's rounding, twice: |x| up to 710, in FP32 up to 2
+    tol = 1e-12 if dt == "f64" else 1e-5
+    for k in range(n):
+        assert torch.allclose(got[k], want[k], rtol=tol, atol=0.0, equal_nan=True), (
+            rho[k], s[k], got[k], want[k])
