@@ -946,8 +946,11 @@ __device__ __forceinline__ TileWalk tile_walk(const int n) {
   return TileWalk{lo + (b >> 3), (g - x + 7) >> 3, hi};
 }
 
+// FP64 takes 186 registers here, so two waves per SIMD: held to three it spills 14
+// of them in every row (us per step, three -> two waves: 12 x 200^2 on 192 x 16
+// strips 70 -> 57, 4 x 1024^2 on 64 x 64 304 -> 218, on 128 x 32 215 -> 198).
 template <int CW>
-__global__ __launch_bounds__(CW + 64) __attribute__((amdgpu_waves_per_eu(HLBM_IS_F32 ? 4 : 3)))
+__global__ __launch_bounds__(CW + 64) __attribute__((amdgpu_waves_per_eu(HLBM_IS_F32 ? 4 : 2)))
 void k_step_batch(BatchArgs a) {
   __shared__ LevelRings<CW + 4> R;
   const TileWalk walk = tile_walk(a.nitems);
