@@ -85,7 +85,7 @@ def f64_same_config(n, fields, tile_w, tile_h, steps=100, keep=None):
     With `keep` (a list) the solver is appended to it instead of freed."""
     import torch
 
-    from paper_2002_03644_amd import Params, Solver, launch_shape
+    from paper_2002_03644_amd import Params, Solver, step_plan
     r, u, v, t = fields
     S = Solver(Params(n, n, dtype="f64", mu=1e-3, sigma=0.0, tile_w=tile_w, tile_h=tile_h),
                r, u, v, theta=t)
@@ -105,7 +105,7 @@ def f64_same_config(n, fields, tile_w, tile_h, steps=100, keep=None):
     if keep is None:
         torch.cuda.empty_cache()
     gbs = 2 * BYTES_PER_NODE * n * n / (ms / 1e3) / 1e9
-    tw, th = launch_shape(Params(n, n, dtype="f64", tile_w=tile_w, tile_h=tile_h))
+    tw, th = step_plan(Params(n, n, dtype="f64", tile_w=tile_w, tile_h=tile_h))["tile"]
     return {"mlups": round(n * n / (ms / 1e3) / 1e6, 1), "ms_per_step": round(ms, 4),
             "achieved": round(gbs, 1), "unit": "GB/s", "frac": round(gbs / HBM_PEAK_GBS, 4),
             "steps": steps, "status_after": int(code), "tile_w": tw, "tile_h": th}
@@ -234,14 +234,17 @@ def main():
     import torch
 
     import hlbm_inputs as hi
-    from paper_2002_03644_amd import Params, Solver, launch_plan
+    from paper_2002_03644_amd import Params, Solver, step_plan
 
     n = args.n
     print(f"[bench] generating {n}x{n} turbulence", file=sys.stderr, flush=True)
     r, u, v, t = hi.turbulence(n, 0.5, hi.THETA_PAPER, seed=0)
     params = Params(n, n, dtype="f32", mu=1e-3, sigma=0.0, tile_w=args.tile_w,
                     tile_h=args.tile_h, steps_per_launch=args.steps_per_launch)
-    spl, tile_w, tile_h = launch_plan(params)
+    plan = step_plan(params)
+    spl, (tile_w, tile_h) = plan["steps_per_launch"], plan["tile"]
+    if plan["kernel"] == "resident":  # one launch takes up to that many steps
+        spl = min(spl, args.steps)
     dev = torch.device("cuda:0")
     fields = [torch.from_numpy(a.astype(np.float32)).to(dev) for a in (r, u, v, t)]
     S = Solver(params, *fields[:3], theta=fields[3], device=dev)
@@ -282,16 +285,22 @@ def main():
     # the dominant kernel does `spl` lattice updates of every node per
     # launch; its algorithmic bytes per launch are 80 B x nodes x spl, and
     # its average launch duration is the timed region over its launches
-    launches = args.steps // spl
+    launches = args.steps // spl + args.steps % spl  # a rest as single steps
     bytes_per_launch = BYTES_PER_NODE * nodes * spl
     ms_per_launch = ms_per_step * spl
     achieved = bytes_per_launch / (ms_per_launch / 1e3) / 1e9
-    traffic = measured_traffic(nodes, spl) if args.steps % spl == 0 else None
-    roofline = {"bound": "hbm", "kernel": KERNEL_NAMES[spl].format(w=tile_w),
+    traffic = measured_traffic(nodes, spl) if spl in TRAFFIC_FILES and args.steps % spl == 0 else None
+    kernel = ("hlbm::f32::k_resident" if plan["kernel"] == "resident"
+              else KERNEL_NAMES[spl].format(w=tile_w))
+    roofline = {"bound": "hbm", "kernel": kernel,
                 "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": traffic, "steps_per_launch": spl, "launches": launches,
                 "algorithmic_bytes_per_launch": bytes_per_launch,
+                # a launch of several steps reads and writes the state once: what it
+                # needs of the memory, beside the bytes of its steps one by one
+                "state_pass_bytes": BYTES_PER_NODE * nodes,
+                "state_pass_frac": round(achieved / spl / HBM_PEAK_GBS, 4),
                 "ms_per_launch": round(ms_per_launch, 5)}
 
     if args.copy_calibration:

@@ -80,8 +80,7 @@ typedef struct {
                            too with steps_per_launch = 2, whose workgroup is tile_w + 8
                            lanes rounded up to whole waves), 0 = auto */
   int32_t tile_h;       /* output rows per workgroup strip (>= 1), 0 = auto;
-                           hlbm_launch_shape reports the shape (with both
-                           automatic, the nominal one: see there) */
+                           hlbm_step_plan reports what a step will use */
   double gamma;         /* heat-capacity ratio, > 1 */
   double prandtl;       /* Prandtl number, > 0; lambda = mu c_p / Pr */
   double mu;            /* dynamic viscosity, >= 0; local tau = mu / p */
@@ -138,23 +137,19 @@ size_t hlbm_state_bytes(const hlbm_params *p);
 /* Check parameters without touching the GPU: HLBM_OK or HLBM_EINVAL. */
 int hlbm_validate(const hlbm_params *p);
 
-/* Tile shape of hlbm_step's launches for these parameters (of the two-step
+/* Nominal tile shape of hlbm_step for these parameters (of the two-step
  * sweep when hlbm_launch_plan reports two steps per launch): tile_w / tile_h
  * as given, or the defaults when they are 0.  One step per launch:
  * 192-column tiles from 1024 columns, 128 below, 64 for nx <= 64; 16-row
  * strips at 192 columns in FP32, 32 otherwise, halved down to 4 rows until
  * about 768 workgroups exist in FP32 or 512 in FP64; never more rows than
- * ny.  Writes *host_tile_w and *host_tile_h; HLBM_OK, or HLBM_EINVAL if the
- * parameters are invalid or a pointer is NULL.  These are the nominal shapes:
- * with tile_w and tile_h both 0, hlbm_step fits width and height to whole
- * rounds of the device's resident workgroups on grids of fewer than four such
- * rounds, and there also takes FP32 domains periodic along both axes two steps
- * at a time below 900,000 nodes unless steps_per_launch is 1, and domains of at
- * most 1024 nodes (counting a ghost ring on clamped axes) all at once in one
- * workgroup unless steps_per_launch is given (results are the same bit for bit).  Host-only; callable without a GPU. */
+ * ny.  A given shape is launched as it is; with tile_w and tile_h both 0
+ * hlbm_step may launch another (see hlbm_step_plan).  Writes *host_tile_w and
+ * *host_tile_h; HLBM_OK, or HLBM_EINVAL if the parameters are invalid or a
+ * pointer is NULL.  Host-only; callable without a GPU. */
 int hlbm_launch_shape(const hlbm_params *p, int32_t *host_tile_w, int32_t *host_tile_h);
 
-/* Launch plan of hlbm_step for these parameters: steps per kernel launch (1
+/* Nominal launch plan for these parameters: steps per kernel launch (1
  * or 2, see steps_per_launch) and the tile shape of that launch (for two
  * steps per launch: tile_w / tile_h as given, or 184-column tiles from 1024
  * columns in FP32, with the tallest strips of 64, 32, 16 or 8 rows that give
@@ -162,11 +157,30 @@ int hlbm_launch_shape(const hlbm_params *p, int32_t *host_tile_w, int32_t *host_
  * least three quarters; 120 columns from 640 columns in FP32, halved down to
  * 8 rows until 768 workgroups exist; 128 columns otherwise, 64 for nx <= 64,
  * with 64-row strips halved down to 8 rows until about 384 workgroups
- * exist).  HLBM_OK, or
- * HLBM_EINVAL if the parameters are invalid or a pointer is NULL.
- * Host-only. */
+ * exist).  What hlbm_step launches with tile_w and tile_h both 0 is
+ * hlbm_step_plan's.  HLBM_OK, or HLBM_EINVAL if the parameters are invalid or a
+ * pointer is NULL.  Host-only. */
 int hlbm_launch_plan(const hlbm_params *p, int32_t *host_steps_per_launch, int32_t *host_tile_w,
                      int32_t *host_tile_h);
+
+/* What hlbm_step launches for these parameters.  With tile_w and tile_h both 0
+ * it starts from the nominal plan, fits width and height to whole rounds of the
+ * device's resident workgroups on grids of fewer than four such rounds, takes
+ * FP32 domains periodic along both axes two steps at a time also below 900,000
+ * nodes (unless steps_per_launch is 1), and holds domains of at most 1024 nodes
+ * (counting a ghost ring on clamped axes) in one workgroup for all steps of a
+ * call unless steps_per_launch is given.  Results do not depend on the plan, bit
+ * for bit.
+ *   host_kernel           an hlbm_step_kernel
+ *   host_steps_per_launch 1 or 2; HLBM_STEP_RESIDENT: the most one launch takes
+ *   host_tile_w, _h       output columns and rows of a workgroup in such a launch
+ *   host_single_w, _h     the same of a single step's launch (an odd last step)
+ * HLBM_OK, or HLBM_EINVAL if the parameters are invalid or a pointer is NULL.
+ * Host-only; callable without a GPU. */
+typedef enum { HLBM_STEP_SWEEP = 0, HLBM_STEP_RESIDENT = 1 } hlbm_step_kernel;
+int hlbm_step_plan(const hlbm_params *p, int32_t *host_kernel, int32_t *host_steps_per_launch,
+                   int32_t *host_tile_w, int32_t *host_tile_h, int32_t *host_single_w,
+                   int32_t *host_single_h);
 
 /* Initialise a domain from macroscopic fields (algorithm of Sec. 3.5, steps
  * 1-4): F0 = f^eq + f^1[a1FD] - psi/2 at every node, so the first step sees
@@ -182,8 +196,8 @@ int hlbm_init(hlbm_handle **out, const hlbm_params *p, void *workspace, size_t w
               const void *rho, const void *ux, const void *uy, const void *s,
               hlbm_stream_t stream);
 
-/* Enqueue nsteps (>= 0) time steps (Sec. 3.5, steps 5-11), one or two per
- * kernel launch as hlbm_launch_plan reports.  Asynchronous.
+/* Enqueue nsteps (>= 0) time steps (Sec. 3.5, steps 5-11) in the launches that
+ * hlbm_step_plan reports.  Asynchronous.
  * With bc_y = HLBM_BC_WALL every step (and hlbm_init) ends by rebuilding the
  * two wall rows, a regularised wet-node wall (our reading of the wall
  * condition of the thermal Couette case, Sec. 4.4, which the paper cites

@@ -65,6 +65,7 @@ def lib():
             "hlbm_launch_shape": (ctypes.c_int, [PP, ctypes.POINTER(i32), ctypes.POINTER(i32)]),
             "hlbm_launch_plan": (ctypes.c_int, [PP, ctypes.POINTER(i32), ctypes.POINTER(i32),
                                                 ctypes.POINTER(i32)]),
+            "hlbm_step_plan": (ctypes.c_int, [PP] + 6 * [ctypes.POINTER(i32)]),
             "hlbm_validate": (ctypes.c_int, [PP]),
             "hlbm_init": (ctypes.c_int, [ctypes.POINTER(vp), PP, vp, sz, vp, vp, vp, vp, vp]),
             "hlbm_step": (ctypes.c_int, [vp, i32, vp]),
@@ -199,7 +200,7 @@ def workspace_bytes(p: Params) -> int:
 
 
 def launch_shape(p: Params):
-    """(tile_w, tile_h) that the single-domain step launches for p."""
+    """Nominal (tile_w, tile_h) of the single-domain step for p (see step_plan)."""
     cp = p.c()
     w, h = ctypes.c_int32(), ctypes.c_int32()
     _check(lib().hlbm_launch_shape(ctypes.byref(cp), ctypes.byref(w), ctypes.byref(h)),
@@ -208,12 +209,25 @@ def launch_shape(p: Params):
 
 
 def launch_plan(p: Params):
-    """(steps_per_launch, tile_w, tile_h) of hlbm_step for p."""
+    """Nominal (steps_per_launch, tile_w, tile_h) of hlbm_step for p (see step_plan)."""
     cp = p.c()
     n, w, h = ctypes.c_int32(), ctypes.c_int32(), ctypes.c_int32()
     _check(lib().hlbm_launch_plan(ctypes.byref(cp), ctypes.byref(n), ctypes.byref(w),
                                   ctypes.byref(h)), "hlbm_launch_plan")
     return int(n.value), int(w.value), int(h.value)
+
+
+def step_plan(p: Params):
+    """What Solver.step launches for p: dict of ``kernel`` ("sweep" or
+    "resident"), ``steps_per_launch``, ``tile`` (columns, rows) and
+    ``single_tile`` of a single step's launch."""
+    cp = p.c()
+    v = [ctypes.c_int32() for _ in range(6)]
+    _check(lib().hlbm_step_plan(ctypes.byref(cp), *(ctypes.byref(x) for x in v)),
+           "hlbm_step_plan")
+    k, n, w, h, w1, h1 = (int(x.value) for x in v)
+    return {"kernel": ("sweep", "resident")[k], "steps_per_launch": n, "tile": (w, h),
+            "single_tile": (w1, h1)}
 
 
 def _stream(stream=None):

@@ -292,6 +292,25 @@ int hlbm_launch_plan(const hlbm_params *p, int32_t *host_steps_per_launch, int32
   return HLBM_OK;
 }
 
+int hlbm_step_plan(const hlbm_params *p, int32_t *host_kernel, int32_t *host_steps_per_launch,
+                   int32_t *host_tile_w, int32_t *host_tile_h, int32_t *host_single_w,
+                   int32_t *host_single_h) {
+  if (!host_kernel || !host_steps_per_launch || !host_tile_w || !host_tile_h ||
+      !host_single_w || !host_single_h || hlbm_validate(p) != HLBM_OK)
+    return HLBM_EINVAL;
+  hlbm_handle h{};
+  h.p = *p;
+  plan_launches(&h);
+  const hlbm::TileShape &t = h.spl == 2 ? h.tile2 : h.tile;
+  *host_kernel = h.resident ? HLBM_STEP_RESIDENT : HLBM_STEP_SWEEP;
+  *host_steps_per_launch = h.resident ? hlbm::kResidentSteps : h.spl;
+  *host_tile_w = h.resident ? p->nx : t.bw;
+  *host_tile_h = h.resident ? p->ny : t.rows;
+  *host_single_w = h.resident ? p->nx : h.tile.bw;
+  *host_single_h = h.resident ? p->ny : h.tile.rows;
+  return HLBM_OK;
+}
+
 size_t hlbm_workspace_bytes(const hlbm_params *p) {
   if (hlbm_validate(p) != HLBM_OK) return 0;
   return layout_of(p).total;

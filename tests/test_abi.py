@@ -346,3 +346,63 @@ def test_default_plans_are_built_shapes():
                     assert tw in built, (dt, bc, nx, ny, spl, tw)
                     assert 1 <= th <= ny, (dt, bc, nx, ny, spl, th)
                     assert spl == 1 or (bc == "periodic" and dt == "f32"), (dt, bc, nx, ny)
+
+
+def test_step_plans_are_built_shapes():
+    """What hlbm_step launches, over grids from 1 x 1 to 15446^2, both types and
+    all boundaries: tile widths that the kernels are built for, strips of at least
+    one row and at most ny, one workgroup for domains of up to 1024 nodes with the
+    ghosts of clamped axes, two steps per launch for FP32 periodic along both
+    axes."""
+    from paper_2002_03644_amd import step_plan
+    sizes = [1, 2, 5, 31, 64, 65, 100, 200, 511, 640, 768, 1000, 1024, 1031, 1500, 2048, 3000,
+             4096, 6000, 8192, 15446]
+    for dt in ("f32", "f64"):
+        for opts in ({}, dict(bc_x="extrapolate"), dict(bc_y="extrapolate"),
+                     dict(bc_y="wall", wall_theta=0.2)):
+            for nx in sizes:
+                for ny in (4, 7, 64, 300, 3000, nx):
+                    if 9 * nx * ny >= 2 ** 31 or ny < 4 and "bc_y" in opts:
+                        continue
+                    case = (dt, opts, nx, ny)
+                    q = step_plan(_params(nx=nx, ny=ny, dtype=dt, **opts))
+                    ext = (nx + 2 * ("bc_x" in opts)) * (ny + 2 * ("bc_y" in opts))
+                    assert (q["kernel"] == "resident") == (ext <= 1024), case
+                    if q["kernel"] == "resident":
+                        assert q["tile"] == (nx, ny) and q["steps_per_launch"] == 4096, case
+                        continue
+                    two = not opts and dt == "f32"
+                    assert q["steps_per_launch"] == (2 if two else 1), case
+                    one = (64, 128, 192, 256) if dt == "f32" else (64, 128, 192)
+                    assert q["tile"][0] in ((64, 120, 184) if two else one), (case, q)
+                    assert q["single_tile"][0] in one, (case, q)
+                    assert 1 <= q["tile"][1] <= ny and 1 <= q["single_tile"][1] <= ny, (case, q)
+
+
+def test_step_plan_takes_what_is_given_and_rejects_bad_input():
+    import ctypes as C
+
+    from paper_2002_03644_amd import launch_plan, step_plan
+    from paper_2002_03644_amd._lib import lib
+    q = step_plan(_params(nx=8192, ny=8192))          # many rounds: the nominal plan
+    assert (q["steps_per_launch"],) + q["tile"] == launch_plan(_params(nx=8192, ny=8192))
+    assert q["single_tile"] == (192, 16)
+    q = step_plan(_params(nx=20, ny=20, tile_w=128, tile_h=7))
+    assert (q["kernel"], q["steps_per_launch"], q["tile"]) == ("sweep", 1, (128, 7))
+    q = step_plan(_params(nx=20, ny=20, steps_per_launch=2))
+    assert (q["kernel"], q["steps_per_launch"]) == ("sweep", 2)
+    assert step_plan(_params(nx=700, ny=700, steps_per_launch=1))["steps_per_launch"] == 1
+    v = [C.c_int32() for _ in range(6)]
+    p = _params(nx=100, ny=100).c()
+    for k in range(6):
+        args = [C.byref(x) if j != k else None for j, x in enumerate(v)]
+        assert lib().hlbm_step_plan(C.byref(p), *args) != 0
+    bad = _params(nx=100, ny=100, tile_w=100).c()
+    assert lib().hlbm_step_plan(C.byref(bad), *(C.byref(x) for x in v)) != 0
+
+
+def test_bench_reports_the_launched_plan():
+    """The benchmark names kernels and tiles by what a step launches, not by the
+    nominal plan, which automatic launches may replace."""
+    src = open(os.path.join(ROOT, "bench.py")).read()
+    assert "step_plan(" in src and "launch_plan" not in src and "launch_shape" not in src
