@@ -128,9 +128,13 @@ inline long long sweep_cost(long long nb, int rows, int waves, int per_cu, int s
   const int fill = steps == 2 ? 8 : 4;
   const int resident = kModelCUs * per_cu;
   auto iter = [&](int wgs) {  // half waves per SIMD of the fullest CUs, as an index
-    int k = ((wgs + kModelCUs - 1) / kModelCUs * waves + 1) / 2 - 1;
-    // four groups' pairs a CU: not yet at its instruction rate while a third of
-    // the CUs hold three
+    int per = (wgs + kModelCUs - 1) / kModelCUs;
+    // two FP64 workgroups of two waves share a CU's first two SIMDs, and a row takes
+    // as long as with three (2.33 us against 1.75 with one, 2.36 with three)
+    if (waves == 2 && per == 2 && elem_size == 8) per = 3;
+    int k = (per * waves + 1) / 2 - 1;
+    // four groups' pairs a CU: not yet at its instruction rate while a tenth of the
+    // slots are empty (two CUs of five then hold three)
     if (split && k == last && 10 * wgs <= 9 * resident) --k;
     return time[k > last ? last : k];
   };

@@ -379,6 +379,16 @@ def test_step_plans_are_built_shapes():
                     assert 1 <= q["tile"][1] <= ny and 1 <= q["single_tile"][1] <= ny, (case, q)
 
 
+@pytest.mark.parametrize("nx", [1, 16, 64])
+@pytest.mark.parametrize("ny", [700, 1500, 2000, 2500, 2641, 3000, 3014, 4000, 6000])
+def test_fp64_thin_grids_leave_no_two_workgroups_to_a_compute_unit(nx, ny):
+    """Two workgroups of two waves on a compute unit run a row no faster than three
+    (they share two SIMDs); such shapes were 5 to 9 % slower than before the fit."""
+    from paper_2002_03644_amd import step_plan
+    w, h = step_plan(_params(nx=nx, ny=ny, dtype="f64"))["tile"]
+    assert w != 64 or -(-(-(-ny // h)) // 256) != 2, (w, h)
+
+
 def test_step_plan_takes_what_is_given_and_rejects_bad_input():
     import ctypes as C
 
