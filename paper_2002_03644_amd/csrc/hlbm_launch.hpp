@@ -116,6 +116,7 @@ inline TileShape step2_tile(int nx, int ny, int tile_w, int tile_h, int elem_siz
 // below about two waves it hardly rises, the sweep then waits on its own
 // latencies).
 constexpr int kModelCUs = 256;
+constexpr long long kLastLevelCache = 256LL << 20;  // bytes
 inline long long sweep_cost(long long nb, int rows, int waves, int per_cu, int steps,
                             int elem_size, bool split = false) {
   static const int t_split[] = {110, 118, 126, 134, 152, 154, 177, 212};  // two-step, two groups
@@ -153,9 +154,15 @@ inline long long sweep_cost(long long nb, int rows, int waves, int per_cu, int s
 // 9.2, 200^2 9.9 -> 5.9, 2048^2 55.2 -> 50.4; one-step 2048 x 512 26.8 -> 23.9;
 // FP64 600^2 25.8 -> 23.7, 200^2 13.9 -> 11.4.
 //
-// Grids of at least four full rounds of nominal tiles keep those: their rounds
-// even out and memory bounds them (8192^2: 64 rows 631 us per step, 48 644,
-// 96 697).
+// The model has no term for memory, so two kinds of grids keep the nominal shape:
+//  - one-step FP32 sweeps of a state larger than the last-level cache (one buffer
+//    of ten planes), where 192 x 16 is best or level: us per step, nominal against
+//    fitted, 3000^2 159 / 161, 3500^2 213 / 241, 4096^2 281 / 283; below that the
+//    fit wins (2500^2 115 / 113, 6000 x 1000 109 / 107, 2048^2 82.5 / 80);
+//  - grids of at least four full rounds of nominal tiles (8192^2: 64 rows 631 us
+//    per step, 48 644, 96 697).  Nominal strips cut short to fill their last
+//    round reach four rounds early: 2400^2 to 2500^2 stay on 184 x 8, which the model
+//    puts at 1.7 to 1.8 times its best shape.
 struct FitShape {
   int bw, waves, per_cu, max_nx;  // width, waves per workgroup, resident workgroups per CU
   bool split = false;             // two groups of waves (two-step sweep)
@@ -171,6 +178,7 @@ inline TileShape fit_tile(int nx, int ny, const TileShape &nominal, int elem_siz
   auto tiles = [&](int bw, int rows) {
     return (long long)((nx + bw - 1) / bw) * ((ny + rows - 1) / rows);
   };
+  if (steps == 1 && elem_size == 4 && 40LL * nx * ny > kLastLevelCache) return nominal;
   for (int k = 0; k < count; ++k)
     if (shapes[k].bw == nominal.bw &&
         tiles(nominal.bw, nominal.rows) >= 4LL * kModelCUs * shapes[k].per_cu)
