@@ -930,20 +930,23 @@ struct BatchArgs {
 // This workgroup's share of the persistent walk over n items: items first,
 // first + step, ... below end.  Workgroups are dealt round-robin to the
 // eight XCDs (workgroup b to XCD b mod 8); with at least eight workgroups XCD x
-// gets the contiguous item range [x n / 8, (x + 1) n / 8), taken in order by its
-// workgroups, so tiles and strips that share halo rows and columns, and the cache
-// lines their rows share, go through one L2: 8 x 256^2 two-step tiles 14.3 -> 13.2
-// us per step, 8 x 128^2 7.6 -> 5.8; also batches larger than the last-level cache
-// (16 x 1024^2 strips 189 -> 181, 48 mixed domains 81.8 -> 80.5).
+// gets a contiguous eighth of the items, taken in order by its workgroups, so
+// tiles and strips that share halo rows and columns, and the cache lines their rows
+// share, go through one L2: 8 x 256^2 two-step tiles 14.3 -> 13.2 us per step, 8 x
+// 128^2 7.6 -> 5.8; also batches larger than the last-level cache (two-step FP32
+// strips: 16 x 1024^2 203 -> 192).  The first n mod 8 XCDs, which have a workgroup
+// more where each workgroup takes one item, get the item more: shares rounded
+// otherwise leave one workgroup two items in a row (2 x 1024^2 FP64 on 192 x 28
+// strips, 444 items: 142 us per step).
 struct TileWalk {
   int first, step, end;
 };
 __device__ __forceinline__ TileWalk tile_walk(const int n) {
   const int g = (int)gridDim.x, b = (int)blockIdx.x;
   if (g < 8) return TileWalk{b, g, n};
-  const int x = b & 7;
-  const int lo = (int)((long long)x * n / 8), hi = (int)((long long)(x + 1) * n / 8);
-  return TileWalk{lo + (b >> 3), (g - x + 7) >> 3, hi};
+  const int x = b & 7, per = n >> 3, more = n & 7;
+  const int lo = x * per + min(x, more);
+  return TileWalk{lo + (b >> 3), (g - x + 7) >> 3, lo + per + (x < more ? 1 : 0)};
 }
 
 // FP64 takes 186 registers here, so two waves per SIMD: held to three it spills 14
