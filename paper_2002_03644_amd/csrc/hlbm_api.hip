@@ -702,7 +702,19 @@ int batch_resident(const hlbm_batch *b, int tw) {
                               : hlbm::f32::batch_blocks_per_cu(tw);
 }
 
-// Strip shapes by modelled time (see sweep_cost), at most four heights of a width.
+// Modelled time (see sweep_cost) of strips tw x th, per_cu of them resident.
+long long strips_cost(const hlbm_batch *b, int tw, int th, int per_cu) {
+  const int waves = b->spl_strips == 2 ? (tw + 8 + 63) / 64 : (tw + 64) / 64;
+  long long nb = 0;
+  for (const hlbm_params &p : b->params) {
+    const int rows = std::min(th, (int)p.ny);
+    nb += (long long)((p.nx + tw - 1) / tw) * ((p.ny + rows - 1) / rows);
+  }
+  return hlbm::sweep_cost(nb, th, waves, per_cu, b->spl_strips,
+                          (int)elem_size(b->dtype));
+}
+
+// Strip shapes by modelled time, at most four heights of a width.
 struct BatchShape {
   int kind, w, h;
   long long cost;
@@ -712,19 +724,10 @@ std::vector<BatchShape> ranked_strips(const hlbm_batch *b) {
   std::vector<BatchShape> all;
   for (int tw : kBatchTileW) {
     const int per_cu = batch_resident(b, tw);
-    const int waves = b->spl_strips == 2 ? (tw + 8 + 63) / 64 : (tw + 64) / 64;
     std::vector<BatchShape> of_width;
-    for (int th : kTuneRows) {
-      if (!batch_shape_ok(b, HLBM_BATCH_STRIPS, tw, th)) continue;
-      long long nb = 0;
-      for (const hlbm_params &p : b->params) {
-        const int rows = std::min(th, (int)p.ny);
-        nb += (long long)((p.nx + tw - 1) / tw) * ((p.ny + rows - 1) / rows);
-      }
-      const int es = (int)elem_size(b->dtype);
-      of_width.push_back({HLBM_BATCH_STRIPS, tw, th,
-                          hlbm::sweep_cost(nb, th, waves, per_cu, b->spl_strips, es)});
-    }
+    for (int th : kTuneRows)
+      if (batch_shape_ok(b, HLBM_BATCH_STRIPS, tw, th))
+        of_width.push_back({HLBM_BATCH_STRIPS, tw, th, strips_cost(b, tw, th, per_cu)});
     std::stable_sort(of_width.begin(), of_width.end(), cheaper);
     of_width.resize(std::min<size_t>(of_width.size(), 4));
     all.insert(all.end(), of_width.begin(), of_width.end());
@@ -738,11 +741,22 @@ std::vector<BatchShape> ranked_strips(const hlbm_batch *b) {
 // the resident rows over it; 8192^2: 64 rows 631 us per step, 96 697).  A fixed
 // 128 x 32 took 670 us for two steps of 16 x 1024^2 domains, the modelled shape
 // 375.
+//
+// One step per launch past the cache: memory bounds it, which the model leaves out.
+// FP32 starts on 128 x 32, within 3 % of the best shape in most cases where the
+// modelled 256 columns were 2 to 14 % behind (us per step: 4 x 2048^2 304 against
+// 328, 64 x 256^2 88 / 97, 64 domains of 142 to 1024 columns 491 / 569); FP64 where
+// the model does not see at least a tenth in another shape (2 x 1024^2 109 / 142; 12 x
+// 1024^2 557 / 486 and takes the modelled).
 BatchShape initial_strips(const hlbm_batch *b) {
-  const bool large = 2 * b->state_bytes > ((size_t)256 << 20);
+  const bool large = 2 * b->state_bytes > (size_t)hlbm::kLastLevelCache;
+  const BatchShape plain{HLBM_BATCH_STRIPS, 128, 32,
+                         strips_cost(b, 128, 32, batch_resident(b, 128))};
+  if (large && b->spl_strips == 1 && b->dtype == HLBM_F32) return plain;
   for (const BatchShape &s : ranked_strips(b))
-    if (!large || s.h <= 64) return s;
-  return BatchShape{HLBM_BATCH_STRIPS, 128, 32, 0};
+    if (!large || s.h <= 64)
+      return large && b->spl_strips == 1 && 10 * s.cost > 9 * plain.cost ? plain : s;
+  return plain;
 }
 
 // Item list and grids of shape (kind, tw, th); the shape must be one

@@ -270,3 +270,12 @@ def test_divergence_mid_launch_leaves_healthy_domains_bitwise():
             for key in ("rho", "ux", "uy", "s"):
                 assert torch.equal(mb[k][key], ms[j][key]), (tw, th_, k, key)
         del B
+
+
+@pytest.mark.parametrize("dtype,count,n", [("f32", 4, 1024), ("f32", 64, 256), ("f64", 2, 1024)])
+def test_large_one_step_batches_start_on_128_by_32(dtype, count, n):
+    """Batches larger than the last-level cache that take one step per launch: the
+    launch model has no term for memory, and its shapes were up to 14 % slower."""
+    f = hi.uniform(n, n)
+    p = Params(n, n, dtype=dtype, bc_x="extrapolate")
+    assert BatchSolver([p] * count, [f] * count).plan() == (1, "strips", 128, 32)
