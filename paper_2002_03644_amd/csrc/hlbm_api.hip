@@ -759,6 +759,43 @@ BatchShape initial_strips(const hlbm_batch *b) {
   return plain;
 }
 
+// Order of the items over the walk (see tile_walk, which gives each of the eight
+// XCDs a contiguous eighth).  Where an eighth has a fifth more work than the mean (a
+// few large domains before many small ones) a batch larger than the last-level
+// cache deals its items to the XCDs in turn instead.  us per step, eighths against
+// dealt, a 2048^2 domain and 300 of 48^2: two-step strips 64 x 64 140 / 102, 120 x 56
+// 80 / 74, one-step 192 x 40 136 / 121, FP64 64 x 64 406 / 331; eighths within a fifth of
+// each other are better as they are, also of uneven domains (64 of 142 to 1024
+// columns on 184 x 32: 335 / 406).
+void deal_items(const hlbm_batch *b, int tw, int th, std::vector<int> *items) {
+  const int n = (int)items->size() / 4;
+  if (n < 16 || 2 * b->state_bytes <= (size_t)hlbm::kLastLevelCache) return;
+  const int halo = b->spl_strips == 2 ? 8 : 4;
+  auto first = [&](int x) { return x * (n >> 3) + std::min(x, n & 7); };  // as tile_walk
+  long long most = 0, all = 0;
+  for (int x = 0; x < 8; ++x) {
+    long long work = 0;
+    for (int i = first(x); i < first(x + 1); ++i) {
+      const int *it = items->data() + 4 * i;
+      const hlbm_params &p = b->params[it[0]];
+      const int rows = std::min(th, (int)p.ny);
+      work += (long long)(std::min(tw, p.nx - it[1] * tw) + halo) *
+              (std::min(rows, p.ny - it[2] * rows) + halo);
+    }
+    most = std::max(most, work);
+    all += work;
+  }
+  if (5 * 8 * most <= 6 * all) return;
+  std::vector<int> dealt(items->size());
+  for (int m = 0, i = 0; i < n; ++m)
+    for (int x = 0; x < 8; ++x)
+      if (first(x) + m < first(x + 1)) {
+        memcpy(dealt.data() + 4 * (first(x) + m), items->data() + 4 * i, 4 * sizeof(int));
+        ++i;
+      }
+  items->swap(dealt);
+}
+
 // Item list and grids of shape (kind, tw, th); the shape must be one
 // batch_shape_ok accepts.
 hipError_t batch_upload_items(hlbm_batch *b, int kind, int tw, int th, hipStream_t st) {
@@ -766,6 +803,7 @@ hipError_t batch_upload_items(hlbm_batch *b, int kind, int tw, int th, hipStream
   items.reserve(4 * (size_t)b->max_items);
   b->nitems = batch_items_for(b, tw, th, &items);
   if (b->nitems > b->max_items) return hipErrorInvalidValue;
+  deal_items(b, tw, th, &items);
   hipError_t e = hipMemcpyAsync(b->ws + b->off_items, items.data(), sizeof(int) * items.size(),
                                 hipMemcpyHostToDevice, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);  // host vector must outlive the copy

@@ -279,3 +279,27 @@ def test_large_one_step_batches_start_on_128_by_32(dtype, count, n):
     f = hi.uniform(n, n)
     p = Params(n, n, dtype=dtype, bc_x="extrapolate")
     assert BatchSolver([p] * count, [f] * count).plan() == (1, "strips", 128, 32)
+
+
+@pytest.mark.parametrize("kernel,tile", [("strips", (128, 64)), ("strips", (192, 16)),
+                                         ("tiles", (32, 16))])
+def test_items_dealt_to_the_xcds_equal_single_domains(kernel, tile):
+    """A batch larger than the last-level cache with one large domain and many small
+    ones walks its items in another order (128 x 64: 812 items for more workgroups;
+    192 x 16: rounds of them): every domain still takes each step once."""
+    big, small = hi.random_smooth(2048, 2048, seed=1), hi.random_smooth(48, 48, seed=2)
+    opts = dict(dtype="f32", mu=1e-3, sigma=0.2, bc_x="extrapolate")
+    pb, ps = Params(2048, 2048, **opts), Params(48, 48, **opts)
+    B = BatchSolver([pb] + [ps] * 300, [big] + [small] * 300)
+    B.set_tile(*tile, kernel=kernel)
+    B.step(3, graph=False)
+    got = B.moments()
+    want = singles([dataclasses.replace(p, tile_w=128, tile_h=32) for p in (pb, ps)],
+                   [big, small], 3)
+    assert B.status()[0] == 0
+    for k, w in [(0, want[0])] + [(k, want[1]) for k in range(1, 301)]:
+        for q in ("rho", "ux", "uy", "s"):
+            if kernel == "strips":
+                assert torch.equal(got[k][q], w[q]), (k, q)
+            else:   # FP32 tiles fuse their multiply-adds on their own
+                assert (got[k][q] - w[q]).abs().max() < 2e-5, (k, q)
