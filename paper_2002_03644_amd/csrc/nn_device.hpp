@@ -579,6 +579,15 @@ void k_cnn_fused(FusedArgs a) {
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 
 
+// Between a wave's LDS stores and other lanes' reads of them.  LDS runs a wave's
+// accesses in order, so the hardware needs no wait; the compiler orders a lane's own
+// accesses only, and the fences keep it from moving them across.
+__device__ __forceinline__ void wave_handover() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Two 8-byte transposed reads: pixels 8 g .. 8 g + 7 of this lane's channel.  p:
 // the lane's own word of the first four pixels; step: bytes from there to that of
 // the second four.
@@ -704,7 +713,7 @@ void k_wgrad_hh(WgradArgs a) {
     *(bf16x8 *)(sg + lane * 16) = lg[0];
     *(bf16x8 *)(sg + 1024 + lane * 16) = lg[1];
     if (i < a.rows) load(y + 1);
-    __builtin_amdgcn_wave_barrier();
+    wave_handover();
     const bool in_strip = i + 1 < a.rows;
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb) {
@@ -726,7 +735,7 @@ void k_wgrad_hh(WgradArgs a) {
             c = mfma(gf[2 - dy][cb], bf, c);
           }
       }
-    __builtin_amdgcn_wave_barrier();
+    wave_handover();
   }
   if (!u.live)
 #pragma unroll
@@ -794,9 +803,9 @@ void k_wgrad_hn(WgradArgs a) {
   };
   auto narrow_frag = [&]() {
     if (lane < 34) *(bf16x4 *)(sn + lane * 8) = ln;
-    __builtin_amdgcn_wave_barrier();
+    wave_handover();
     const bf16x8 f = read_tr(sn + nword, 4 * 2 * kIn);
-    __builtin_amdgcn_wave_barrier();
+    wave_handover();
     return f;
   };
   f32x4 acc[NT];
@@ -829,7 +838,7 @@ void k_wgrad_hn(WgradArgs a) {
       if constexpr (kL1) acc[6 + wb] = mfma(wf, one, acc[6 + wb]);
     }
     if constexpr (!kL1) acc[6] = mfma(one, nf[1], acc[6]);
-    __builtin_amdgcn_wave_barrier();
+    wave_handover();
   }
   if (!u.live)
 #pragma unroll
