@@ -108,3 +108,24 @@ def test_network_workspace_training_and_inference():
     idx = torch.tensor([2, 0], dtype=torch.int32, device="cuda")
     net.loss_grad(x, tgt, idx=idx)
     assert_intact(buf, nbytes, "network workspace")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("nx,ny,kw", [
+    (2, 100, dict(bc_y="wall", wall_ux_hi=0.02, wall_theta=0.2)), (32, 32, {}), (1, 1, {}),
+    (30, 30, dict(bc_x="extrapolate", bc_y="extrapolate")),
+])
+def test_resident_domain_workspace(nx, ny, kw, dtype):
+    """Domains that one workgroup holds for all steps of a call: written in place
+    (even) and to the other buffer (odd)."""
+    p = Params(nx, ny, dtype=dtype, mu=5e-2, sigma=0.5, **kw)
+    nbytes = lib().hlbm_workspace_bytes(ctypes.byref(p.c()))
+    buf, ws = guarded(nbytes)
+    r, u, v, t = hi.random_smooth(nx, ny, seed=3, amp=0.01)
+    S = Solver(p, r, u, v, theta=t, workspace=ws)
+    S.step(4)
+    S.step(3)
+    S.step(1)
+    S.moments()
+    S.status()
+    assert_intact(buf, nbytes, "workspace")

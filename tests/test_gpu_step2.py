@@ -193,3 +193,38 @@ def test_captured_even_steps_replay_onwards(nx, ny, steps, opts):
         G.step(4)
         E.step(4)
         assert torch.equal(state(G), state(E)), k
+
+
+@pytest.mark.parametrize("nx,ny,opts", [
+    (19, 27, {}), (2, 100, dict(bc_y="wall", wall_theta=0.2, wall_ux_hi=0.02)),
+])
+@pytest.mark.parametrize("dt", ["f32", "f64"])
+def test_resident_calls_longer_than_a_launch(nx, ny, opts, dt):
+    """4097 steps in one call are two launches of the one-workgroup kernel: the
+    same as in calls of 4000, 96 and 1."""
+    f = hi.random_smooth(nx, ny, seed=nx, amp=0.01, u0=(0.02, 0.0))
+    p = Params(nx, ny, dtype=dt, mu=5e-2, sigma=0.3, **opts)
+    one, three = run(p, f, 4097), run(p, f, 4000)
+    three.step(96)
+    three.step(1)
+    assert one.status()[0] == HLBM_OK and one.steps == three.steps == 4097
+    assert torch.equal(state(one), state(three))
+
+
+@pytest.mark.parametrize("nx,ny", [(19, 27), (32, 32)])
+@pytest.mark.parametrize("dt", ["f32", "f64"])
+def test_resident_divergence_is_kept(nx, ny, dt):
+    """A divergence inside the one-workgroup kernel stays flagged once the state is
+    healthy again, as with the sweeps (the flag, not the final state, tells)."""
+    f = hi.random_smooth(nx, ny, seed=nx, amp=0.02)
+    for opts in ({}, dict(tile_w=64, tile_h=8)):
+        S = run(Params(nx, ny, dtype=dt, mu=2e-3, **opts), f, 2)
+        F, s = S.populations().clone(), S.moments()["s"].clone()
+        bad = F.clone()
+        bad[0, ny - 1, nx - 1] = float("nan")
+        S.set_populations(bad, s)
+        S.step(1)
+        S.set_populations(F, s)
+        assert S.status()[0] == HLBM_EDIVERGED, opts
+        S.step(3)
+        assert S.status()[0] == HLBM_EDIVERGED, opts
