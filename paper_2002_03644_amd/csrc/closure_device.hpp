@@ -162,6 +162,10 @@ __global__ __launch_bounds__(kCorrThreads) void k_corr_apply(CorrArgs a) {
 
 // Macroscopic fields of every domain of a batch in one launch: workgroup
 // column y = domain, fields concatenated at foffs[k] (as k_moments per domain).
+// Memory bound: the waves in flight count.  FP32 gets eight a SIMD from 29 vector
+// registers only up to 80 scalar ones; left alone the compiler takes 81 (one
+// address more kept than formed), and 16 x 1024^2 domains take 238 us for 226.
+// FP64 is bound by its vector registers, of which fewer scalars would cost some.
 struct BatchFieldArgs {
   const DomainArgs *doms;
   const long long *offs, *foffs;
@@ -169,7 +173,8 @@ struct BatchFieldArgs {
   real *rho, *ux, *uy, *s, *theta;
 };
 
-__global__ __launch_bounds__(256) void k_batch_moments(BatchFieldArgs a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_num_sgpr(HLBM_IS_F32 ? 80 : 102)))
+void k_batch_moments(BatchFieldArgs a) {
   const int k = blockIdx.y;
   const DomainArgs &d = a.doms[k];
   const long long n = (long long)d.nx * d.ny, P = d.plane;
