@@ -469,10 +469,11 @@ __device__ __forceinline__ real upwind_gamma(const DomainArgs &d, real u, real g
 //   - the populations along an axis are summed from the terms that cancel first
 //     (rho + 3 Axx), so that no partial sum is larger than it has to be, and
 //     multiplied by their weight last.  With the factor 1/9 carried from the start
-//     and one sum for both axes (15 instructions of 250 less, 1 % of the time at
-//     1500 x 1100, none at 4096^2) a step rounded more than the formulas as they
-//     stand: velocities 2 to 4 % further from 80-bit ones, 7 % from 64-bit ones at
-//     2048^2; this way 3 to 5 % closer, and level.
+//     and one sum for both axes (ten FP64 instructions a node less, 1 % of the time
+//     at 1500 x 1100, none at 4096^2) a step rounded more than the formulas as they
+//     stand: after 20 to 50 steps of eight flows velocities 3 to 7 % and densities
+//     1 to 3 % further from the exact ones; this way velocities level to 2 %
+//     closer, densities level.
 // FP32: deviations from the rest reference formed from deviations (p - p_ref,
 // rho c - rho_ref c_ref, rho c^2 - rho_ref c_ref^2).  Its rounding is kept term
 // by term: E1 is discontinuous in the sign of u, so where a velocity crosses

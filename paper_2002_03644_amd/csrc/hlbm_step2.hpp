@@ -3,8 +3,7 @@
 // hlbm_device.hpp).
 //
 // The one-step sweep reads the ten planes once and writes them once per
-// step; its arithmetic runs far below the chip's VALU rate (doubling it costs
-// 0-6 % of the step time), so the step is bound by the state traffic.  Here
+// step, and on large FP32 grids that traffic bounds it (8192^2: 5.8 TB/s).  Here
 // a workgroup reads the state at level n once and writes level n + 2 once:
 // the per-node arithmetic of each step is the one-step kernel's, in the
 // same order (FP64 results are bitwise those of two single steps), and level
@@ -15,7 +14,7 @@
 // rows), which needs level n on a radius-4 halo: CW + 8 columns, rows + 8
 // rows.  Lanes 0..CW-1 hold the tile's columns (aligned loads and stores),
 // lanes CW..CW+7 the four halo columns on each side; the rest of the last
-// wave only joins the barriers.  A column's ring position is ri = column -
+// wave repeats the first halo column.  A column's ring position is ri = column -
 // (x0 - 4).  Virtual row j is grid row y0 - 4 + j.
 //
 // Stages per level (A: moments, B: collision, C: streaming and entropy, the
@@ -47,8 +46,9 @@
 // level n + 1 of the wrapped node from the wrapped stencil, bit for bit what
 // the node's own lane computes, so periodic domains of any size (including
 // ragged tiles and grids thinner than the halo) are exact.  Clamped
-// boundaries would need the ghost copies of level n + 1, which this sweep
-// does not form; they and walls take the one-step kernel.
+// boundaries need ghost copies of level n + 1 (along x the edge column's, which is
+// in the ring, along y rows of their own), which this sweep does not form; they
+// and walls take the one-step kernel.
 #pragma once
 
 namespace hlbm {
@@ -180,8 +180,8 @@ __device__ __forceinline__ void sweep_tile2(const DomainArgs &d, const real *src
 // iteration lasts as long as one wave's instructions for both levels; half of
 // them a wave, on twice the waves, take 1.2 instead of 1.45 us (one workgroup
 // of 120 columns per CU).  us per step, one group -> two: 200^2 7.1 -> 5.9, 500^2
-// 9.7 -> 9.1, 900^2 15.1 -> 13.8, 1500 x 1100 22.4 -> 20.8; level at 2048^2 and
-// 8192^2.  Wider tiles keep one group: the hand-over leaves 184 columns two
+// 9.7 -> 9.1, 900^2 15.1 -> 13.8, 1500 x 1100 22.4 -> 20.9 (one state, resident
+// in the last-level cache); level at 2048^2 and 8192^2.  Wider tiles keep one group: the hand-over leaves 184 columns two
 // workgroups per CU instead of four (8192^2 629 -> 764).
 template <int CW>
 struct SplitRings2 {
