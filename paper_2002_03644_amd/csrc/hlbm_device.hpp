@@ -470,7 +470,7 @@ __device__ __forceinline__ real upwind_gamma(const DomainArgs &d, real u, real g
 //     (rho + 3 Axx), so that no partial sum is larger than it has to be, and
 //     multiplied by their weight last.  With the factor 1/9 carried from the start
 //     and one sum for both axes (ten FP64 instructions a node less, 1 % of the time
-//     at 1500 x 1100, none at 4096^2) a step rounded more than the formulas as they
+//     at 1500 x 1100, 0.4 % at 8192^2) a step rounded more than the formulas as they
 //     stand: after 20 to 50 steps of eight flows velocities 3 to 7 % and densities
 //     1 to 3 % further from the exact ones; this way velocities level to 2 %
 //     closer, densities level.
